@@ -1,10 +1,10 @@
 // 3-D CNN of the learned warm start and mass (include/cnn.h) on gfx950 MFMA.
 //
 // Every 3x3x3 convolution is an implicit GEMM on 16x16x16 bf16 MFMA tiles
-// (float32 accumulation): a wave owns 16 consecutive voxels (rows) and all
-// 16 output channels (columns); the K loop runs over (tap, input channel).
+// (float32 accumulation): 16 output channels (rows) by 16 consecutive voxels
+// (columns); the K loop runs over (tap, input channel).
 // Activations are channels-last bfloat16 [V][4] (input, 3 channels + zero
-// pad) or [V][16]; pre-activations float32 [V][16].
+// pad) or [V][16]; pre-activations float32 [V][16], [V][2] for the last layer.
 // Lane layout of the MFMA (lane l, element i): A[l % 16][4 (l / 16) + i],
 // B[4 (l / 16) + i][l % 16], D[4 (l / 16) + i][l % 16].
 //
@@ -38,6 +38,9 @@ inline int off_w(int l) {
 }
 inline int off_b(int l) { return off_w(l) + 27 * kCin[l] * kCout[l]; }
 inline int n_params() { return off_w(4); }
+// past the gradient, the last layer's bias padded to 16 channels (16-byte aligned)
+inline int off_pad() { return (n_params() + 3) / 4 * 4; }
+inline int n_grad() { return off_pad() + 16; }
 
 __device__ __forceinline__ uint16_t f2bf(float f) {
   uint32_t u = __float_as_uint(f);
@@ -80,147 +83,165 @@ __global__ void __launch_bounds__(256) k_features(long long nv, const float* __r
 
 enum ConvMode : int { C_FWD_GELU = 0, C_FWD_LAST = 1, C_DGRAD = 2 };
 
-// One wave per 16-voxel tile; CS = channel stride of the input (4 or 16),
-// NC = K chunks (7 for the 3-channel input: 4 taps x 4 channels per chunk; 27
-// otherwise).  The chunk loop is unrolled so that every gather of a tile is
-// issued before the first MFMA needs it.  STORE_Z: keep the pre-activation for
-// the backward pass (inference skips it).
-template <int CS, int MODE, int NC, bool STORE_Z>
-__global__ void __launch_bounds__(256) k_conv(int n, const uint16_t* __restrict__ in,
-                                              const bf16x4* __restrict__ wp,
-                                              const float* __restrict__ bias,
-                                              const float* __restrict__ zprev,
-                                              float* __restrict__ zout,
-                                              uint16_t* __restrict__ aout) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const long long nv = (long long)n * n * n;
-  const long long tile = (long long)blockIdx.x * 4 + wave;
-  if (tile * 16 >= nv) return;  // no barriers below
-  const int m = lane & 15, grp = lane >> 4;
-  const long long v = tile * 16 + m;
-  const int x = (int)(v / ((long long)n * n)), y = (int)((v / n) % n), z = (int)(v % n);
-  bf16x4 a[NC];
-#pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    const int tap = CS == 16 ? c : 4 * c + grp;
-    const int ch0 = CS == 16 ? 4 * grp : 0;
-    a[c] = bf16x4{0, 0, 0, 0};
-    if (tap < 27) {
-      const int xx = x + tap / 9 - 1, yy = y + (tap / 3) % 3 - 1, zz = z + tap % 3 - 1;
-      if ((unsigned)xx < (unsigned)n && (unsigned)yy < (unsigned)n && (unsigned)zz < (unsigned)n)
-        a[c] = *reinterpret_cast<const bf16x4*>(in + (((long long)xx * n + yy) * n + zz) * CS + ch0);
-    }
-  }
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int c = 0; c < NC; ++c)
-    acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[c], wp[c * 64 + lane], acc, 0, 0, 0);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const long long vo = tile * 16 + 4 * grp + i;
-    float val = acc[i];
-    if (MODE == C_FWD_GELU) {
-      val += bias[m];
-      if (STORE_Z) zout[vo * 16 + m] = val;
-      aout[vo * 16 + m] = f2bf(gelu(val));
-    } else if (MODE == C_FWD_LAST) {
-      zout[vo * 16 + m] = val + bias[m];
-    } else {
-      aout[vo * 16 + m] = f2bf(val * gelu_grad(zprev[vo * 16 + m]));
-    }
-  }
+// Bricks of the convolutions: BX x BY x 16 voxels (x, y, z) with a one-voxel halo, staged
+// in LDS; every grid side is a multiple of 4, so only y and z can overhang.
+constexpr int kCX = 4, kCY = 8, kBZ = 16;
+constexpr int kCHX = kCX + 2, kCHY = kCY + 2, kHZ = kBZ + 2;
+constexpr int kCHalo = kCHX * kCHY * kHZ;  // voxels of the haloed brick
+
+__host__ __device__ inline int conv_bricks(int n) {
+  return (n / kCX) * ((n + kCY - 1) / kCY) * ((n + kBZ - 1) / kBZ);
 }
 
-// 16-channel layers with the input brick staged in LDS: a block computes a
-// brick of BX x BY x 16 voxels (x, y, z), loading it once with a one-voxel halo;
-// each of its 4 waves takes BX * BY / 4 rows of 16 z-voxels (one MFMA tile each)
-// and reads the 27 shifted A fragments from LDS.  Needs n a multiple of 16.
-constexpr int kBX = 2, kBY = 8, kBZ = 16;
-constexpr int kHX = kBX + 2, kHY = kBY + 2, kHZ = kBZ + 2;
-constexpr int kHalo = kHX * kHY * kHZ;  // voxels of the haloed brick
-template <int MODE, bool STORE_Z>
-__global__ void __launch_bounds__(256) k_conv_lds(int n, const uint16_t* __restrict__ in,
-                                                  const bf16x4* __restrict__ wp,
-                                                  const float* __restrict__ bias,
-                                                  const float* __restrict__ zprev,
-                                                  float* __restrict__ zout,
-                                                  uint16_t* __restrict__ aout) {
-  __shared__ uint4 brick[kHalo * 2];  // [voxel][2 x 8 bf16 channels]
+// Workgroups are dealt to the 8 XCDs round-robin; brick_of gives each XCD a contiguous
+// run of bricks, so that neighbours (which share their halos) meet in one L2.
+__device__ __forceinline__ int brick_of(int b, int g) {
+  const int q = g >> 3, r = g & 7, x = b & 7, i = b >> 3;
+  return x < r ? x * (q + 1) + i : r * (q + 1) + (x - r) * q + i;
+}
+
+// One 3x3x3 convolution (zero padding).  Wave w of a block owns the brick's x plane w: 8
+// rows of 16 z voxels, one accumulator tile each.  The weights are the MFMA's A operand
+// (rows = output channels) and a row's shifted activations its B operand (columns =
+// voxels), so a lane ends up with 4 consecutive output channels of one voxel and stores
+// them together (64 lanes cover 16 whole voxels; with the operands the other way round a
+// store wrote 2 bytes per lane).  K runs over taps, 16 channels at a time (CS = 16), or 4
+// taps x 4 channels (CS = 4: the network's input, read as float32 and rounded here).  A
+// fragment read from LDS serves every row of the wave that needs it (up to 3 of the 8):
+// 90 reads for 216 MFMAs, where one read per MFMA kept LDS as busy as the matrix cores.
+// The order of the products of one output is that of the taps, whatever the brick.
+// What bounds it at 256^3 (kernel trace): the products and the staging (396 us for the
+// last layer) and, for the hidden layers, erfc and the stores (713 us; 763 before, and the
+// last layer 661 us plus 257 us to pick its two channels out of 16 stored ones).
+// TRAIN: keep the pre-activation for the backward pass.  LAST: out0, out1 are the two
+// output channels, or out0 the pairs [V][2] for the loss (TRAIN).
+template <int CS, int MODE, bool TRAIN>
+__global__ void __launch_bounds__(256, 4) k_conv(int n, const void* __restrict__ in,
+                                                 const bf16x4* __restrict__ wp,
+                                                 const float* __restrict__ bias,
+                                                 const float* __restrict__ zprev,
+                                                 float* __restrict__ out0, float* __restrict__ out1,
+                                                 uint16_t* __restrict__ aout) {
+  constexpr int kItems = CS == 16 ? 2 * kCHalo : kCHalo;  // 16-byte halves / whole voxels
+  constexpr int kIter = (kItems + 255) / 256;
+  __shared__ uint4 brick[CS == 16 ? 2 * kCHalo : kCHalo / 2];  // [voxel][CS] bf16
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int nbz = n / kBZ, nby = n / kBY;
-  const int bz = blockIdx.x % nbz, by = (blockIdx.x / nbz) % nby, bx = blockIdx.x / (nbz * nby);
-  const int x0 = bx * kBX, y0 = by * kBY, z0 = bz * kBZ;
-  // stage the brick with its halo (zeros outside the grid)
-  for (int i = threadIdx.x; i < kHalo * 2; i += 256) {
-    const int vox = i >> 1, half = i & 1;
-    const int hz = vox % kHZ, hy = (vox / kHZ) % kHY, hx = vox / (kHZ * kHY);
-    const int xx = x0 + hx - 1, yy = y0 + hy - 1, zz = z0 + hz - 1;
-    uint4 val = make_uint4(0u, 0u, 0u, 0u);
-    if ((unsigned)xx < (unsigned)n && (unsigned)yy < (unsigned)n && (unsigned)zz < (unsigned)n)
-      val = reinterpret_cast<const uint4*>(in + (((long long)xx * n + yy) * n + zz) * 16)[half];
-    brick[i] = val;
-  }
-  bf16x4 w[27];
+  const int nbz = (n + kBZ - 1) / kBZ, nby = (n + kCY - 1) / kCY;
+  const int bk = brick_of(blockIdx.x, gridDim.x);
+  const int x0 = bk / (nbz * nby) * kCX, y0 = bk / nbz % nby * kCY, z0 = bk % nbz * kBZ;
+  const long long nv = (long long)n * n * n;
+  // stage the brick with its halo (zeros outside the grid), every load first
+  uint4 st[CS == 16 ? kIter : 1];
+  float sf[CS == 16 ? 1 : kIter][3];
 #pragma unroll
-  for (int c = 0; c < 27; ++c) w[c] = wp[c * 64 + lane];
+  for (int k = 0; k < kIter; ++k) {
+    const int i = threadIdx.x + 256 * k, vox = CS == 16 ? i >> 1 : i;
+    const int xx = x0 + vox / (kHZ * kCHY) - 1, yy = y0 + vox / kHZ % kCHY - 1, zz = z0 + vox % kHZ - 1;
+    const bool ok = i < kItems && (unsigned)xx < (unsigned)n && (unsigned)yy < (unsigned)n && (unsigned)zz < (unsigned)n;
+    const long long v = ((long long)xx * n + yy) * n + zz;
+    if constexpr (CS == 16) {
+      st[k] = make_uint4(0u, 0u, 0u, 0u);
+      if (ok) st[k] = reinterpret_cast<const uint4*>(in)[2 * v + (i & 1)];
+    } else {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) sf[k][c] = ok ? reinterpret_cast<const float*>(in)[c * nv + v] : 0.f;
+    }
+  }
+  constexpr int NC = CS == 16 ? 27 : 7;
+  bf16x4 w[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) w[c] = wp[c * 64 + lane];
+#pragma unroll
+  for (int k = 0; k < kIter; ++k) {
+    const int i = threadIdx.x + 256 * k;
+    if (i < kItems) {
+      if constexpr (CS == 16)
+        brick[i] = st[k];
+      else
+        reinterpret_cast<ushort4*>(brick)[i] = make_ushort4(f2bf(sf[k][0]), f2bf(sf[k][1]), f2bf(sf[k][2]), 0);
+    }
+  }
   __syncthreads();
   const int m = lane & 15, grp = lane >> 4;
-  const uint16_t* lb = reinterpret_cast<const uint16_t*>(brick);
-  constexpr int kRows = kBX * kBY / 4;
+  const bf16x4* lb = reinterpret_cast<const bf16x4*>(brick);
+  f32x4 acc[kCY];
 #pragma unroll
-  for (int r = 0; r < kRows; ++r) {
-    const int row = wave * kRows + r;  // (x, y) row of the brick
-    const int rx = row / kBY, ry = row % kBY;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int r = 0; r < kCY; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if constexpr (CS == 16) {
 #pragma unroll
-    for (int c = 0; c < 27; ++c) {
-      const int hx = rx + c / 9, hy = ry + (c / 3) % 3, hz = m + c % 3;
-      const bf16x4 a =
-          *reinterpret_cast<const bf16x4*>(lb + ((hx * kHY + hy) * kHZ + hz) * 16 + 4 * grp);
-      acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, w[c], acc, 0, 0, 0);
-    }
-    const long long vrow = ((long long)(x0 + rx) * n + (y0 + ry)) * n + z0;
+    for (int dx = 0; dx < 3; ++dx)
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const long long vo = vrow + 4 * grp + i;
-      float val = acc[i];
-      if (MODE == C_FWD_GELU) {
-        val += bias[m];
-        if (STORE_Z) zout[vo * 16 + m] = val;
-        aout[vo * 16 + m] = f2bf(gelu(val));
-      } else if (MODE == C_FWD_LAST) {
-        zout[vo * 16 + m] = val + bias[m];
-      } else {
-        aout[vo * 16 + m] = f2bf(val * gelu_grad(zprev[vo * 16 + m]));
+      for (int hy = 0; hy < kCHY; ++hy)
+#pragma unroll
+        for (int dz = 0; dz < 3; ++dz) {
+          const bf16x4 b = lb[(((wave + dx) * kCHY + hy) * kHZ + m + dz) * 4 + grp];
+#pragma unroll
+          for (int r = 0; r < kCY; ++r)
+            if (r <= hy && hy <= r + 2)
+              acc[r] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w[(dx * 3 + hy - r) * 3 + dz], b, acc[r], 0, 0, 0);
+        }
+  } else {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int tap = 4 * c + grp;
+      const int at = tap < 27 ? (tap / 9 * kCHY + tap / 3 % 3) * kHZ + tap % 3 : 0;
+#pragma unroll
+      for (int r = 0; r < kCY; ++r) {
+        bf16x4 b = lb[(wave * kCHY + r) * kHZ + m + at];
+        if (c == NC - 1 && tap >= 27) b = bf16x4{0, 0, 0, 0};
+        acc[r] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w[c], b, acc[r], 0, 0, 0);
       }
     }
   }
-}
-
-// mu, log-variance from the last layer's float32 output
-__global__ void __launch_bounds__(256) k_outputs(long long nv, const float* __restrict__ z4,
-                                                 float* __restrict__ mu, float* __restrict__ lv) {
-  for (long long v = (long long)blockIdx.x * 256 + threadIdx.x; v < nv; v += (long long)gridDim.x * 256) {
-    if (mu) mu[v] = z4[v * 16];
-    if (lv) lv[v] = z4[v * 16 + 1];
+  float4 bi = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (MODE != C_DGRAD) bi = *reinterpret_cast<const float4*>(bias + 4 * grp);
+  const int zz = z0 + m;
+#pragma unroll
+  for (int r = 0; r < kCY; ++r) {
+    if (y0 + r >= n || zz >= n) continue;
+    const long long v = ((long long)(x0 + wave) * n + y0 + r) * n + zz;
+    const float4 val = make_float4(acc[r][0] + bi.x, acc[r][1] + bi.y, acc[r][2] + bi.z, acc[r][3] + bi.w);
+    if constexpr (MODE == C_FWD_GELU) {
+      if (TRAIN) reinterpret_cast<float4*>(out0)[v * 4 + grp] = val;
+      reinterpret_cast<ushort4*>(aout)[v * 4 + grp] =
+          make_ushort4(f2bf(gelu(val.x)), f2bf(gelu(val.y)), f2bf(gelu(val.z)), f2bf(gelu(val.w)));
+    } else if constexpr (MODE == C_FWD_LAST) {
+      if (grp == 0) {  // channels 0, 1
+        if (TRAIN) {
+          reinterpret_cast<float2*>(out0)[v] = make_float2(val.x, val.y);
+        } else {
+          if (out0) out0[v] = val.x;
+          if (out1) out1[v] = val.y;
+        }
+      }
+    } else {
+      const float4 zp = reinterpret_cast<const float4*>(zprev)[v * 4 + grp];
+      reinterpret_cast<ushort4*>(aout)[v * 4 + grp] =
+          make_ushort4(f2bf(acc[r][0] * gelu_grad(zp.x)), f2bf(acc[r][1] * gelu_grad(zp.y)),
+                       f2bf(acc[r][2] * gelu_grad(zp.z)), f2bf(acc[r][3] * gelu_grad(zp.w)));
+    }
   }
 }
 
+constexpr int kBX = 2, kBY = 8;  // brick of the weight gradient
+constexpr int kHX = kBX + 2, kHY = kBY + 2;
+constexpr int kHalo = kHX * kHY * kHZ;
+
 // Gaussian NLL per voxel; writes the bf16 output gradient [V][16] and block partials.
-__global__ void __launch_bounds__(256) k_loss(long long nv, const float* __restrict__ z4,
+__global__ void __launch_bounds__(256) k_loss(long long nv, const float2* __restrict__ z4,
                                               const float* __restrict__ target,
-                                              uint16_t* __restrict__ dz4, double* __restrict__ part) {
+                                              uint4* __restrict__ dz4, double* __restrict__ part) {
   __shared__ double red[4];
   double acc = 0.0;
   const float inv = 1.f / (float)nv;
   for (long long v = (long long)blockIdx.x * 256 + threadIdx.x; v < nv; v += (long long)gridDim.x * 256) {
-    const float mu = z4[v * 16], s = z4[v * 16 + 1];
+    const float2 out = z4[v];
+    const float mu = out.x, s = out.y;
     const float d = target[v] - mu, e = expf(-s);
     acc += 0.5 * ((double)d * d * e + s);
-    uint16_t* o = dz4 + v * 16;
-    o[0] = f2bf(-d * e * inv);
-    o[1] = f2bf(0.5f * (1.f - d * d * e) * inv);
-    for (int c = 2; c < 16; ++c) o[c] = 0;
+    uint4* o = dz4 + v * 2;
+    o[0] = make_uint4(f2bf(-d * e * inv) | (uint32_t)f2bf(0.5f * (1.f - d * d * e) * inv) << 16, 0u, 0u, 0u);
+    o[1] = make_uint4(0u, 0u, 0u, 0u);
   }
   for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
@@ -362,9 +383,8 @@ __global__ void __launch_bounds__(256) k_wgrad_lds(int n, const uint16_t* __rest
   if (lane < 16) dbpart[gw * 16 + lane] = db;
 }
 
-// One layer's stored state in float32, [V][cout]: pre-activations (16-wide rows),
-// bf16 activations and bf16 pre-activation gradients (either pointer may be null).
-__global__ void __launch_bounds__(256) k_layer_state(long long nv, int cout,
+// One layer's stored state in float32, [V][cout]: pre-activations (rows of zs), bf16 activations and bf16 pre-activation gradients (either pointer may be null).
+__global__ void __launch_bounds__(256) k_layer_state(long long nv, int cout, int zs,
                                                      const float* __restrict__ z16,
                                                      const uint16_t* __restrict__ a16,
                                                      const uint16_t* __restrict__ dz16,
@@ -373,7 +393,7 @@ __global__ void __launch_bounds__(256) k_layer_state(long long nv, int cout,
   const long long tot = nv * cout;
   for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < tot; i += (long long)gridDim.x * 256) {
     const long long v = i / cout, ch = i % cout;
-    if (z) z[i] = z16[v * 16 + ch];
+    if (z) z[i] = z16[v * zs + ch];
     if (a) a[i] = bf2f(a16[v * 16 + ch]);
     if (dz) dz[i] = bf2f(dz16[v * 16 + ch]);
   }
@@ -531,46 +551,36 @@ hmc_status ensure(cnn_ctx* c, int n) {
   const size_t nv = (size_t)n * n * n;
   CCHK(c, hipMalloc(&c->a0, nv * 4 * sizeof(uint16_t)));
   for (int i = 0; i < 3; ++i) CCHK(c, hipMalloc(&c->a[i], nv * 16 * sizeof(uint16_t)));
-  for (int i = 0; i < 4; ++i) CCHK(c, hipMalloc(&c->z[i], nv * 16 * sizeof(float)));
+  for (int i = 0; i < 4; ++i) CCHK(c, hipMalloc(&c->z[i], nv * (i < 3 ? 16 : 2) * sizeof(float)));
   for (int i = 0; i < 4; ++i) CCHK(c, hipMalloc(&c->dz[i], nv * 16 * sizeof(uint16_t)));
   c->n = n;
   return HMC_OK;
 }
 
-template <bool STORE_Z>
-hmc_status forward_t(cnn_ctx* c, int n, const float* in3) {
+// TRAIN: keeps the pre-activations and the rounded input; out0 / out1: see k_conv
+template <bool TRAIN>
+hmc_status forward_t(cnn_ctx* c, int n, const float* in3, float* mu, float* logvar) {
   const long long nv = (long long)n * n * n;
-  const int blocks = (int)((nv / 16 + 3) / 4);
-  hipLaunchKernelGGL(k_input, dim3(4096), dim3(256), 0, c->stream, nv, in3, c->a0);
-  hipLaunchKernelGGL((k_conv<4, C_FWD_GELU, 7, STORE_Z>), dim3(blocks), dim3(256), 0, c->stream,
-                     n, c->a0, c->wp[0], c->p + off_b(0), nullptr, c->z[0], c->a[0]);
-  const bool lds = n % kBZ == 0;
-  const int lblocks = lds ? (n / kBX) * (n / kBY) * (n / kBZ) : 0;
-  for (int l = 1; l < 3; ++l) {
-    if (lds)
-      hipLaunchKernelGGL((k_conv_lds<C_FWD_GELU, STORE_Z>), dim3(lblocks), dim3(256), 0,
-                         c->stream, n, c->a[l - 1], c->wp[l], c->p + off_b(l), nullptr, c->z[l],
-                         c->a[l]);
-    else
-      hipLaunchKernelGGL((k_conv<16, C_FWD_GELU, 27, STORE_Z>), dim3(blocks), dim3(256), 0,
-                         c->stream, n, c->a[l - 1], c->wp[l], c->p + off_b(l), nullptr, c->z[l],
-                         c->a[l]);
-  }
-  // last layer: bias padded to 16 channels through a small device copy
-  if (lds)
-    hipLaunchKernelGGL((k_conv_lds<C_FWD_LAST, true>), dim3(lblocks), dim3(256), 0, c->stream, n,
-                       c->a[2], c->wp[3], c->g + n_params(), nullptr, c->z[3], nullptr);
-  else
-    hipLaunchKernelGGL((k_conv<16, C_FWD_LAST, 27, true>), dim3(blocks), dim3(256), 0, c->stream,
-                       n, c->a[2], c->wp[3], c->g + n_params(), nullptr, c->z[3], nullptr);
+  const dim3 g(conv_bricks(n)), b(256);
+  if (TRAIN) hipLaunchKernelGGL(k_input, dim3(4096), b, 0, c->stream, nv, in3, c->a0);
+  hipLaunchKernelGGL((k_conv<4, C_FWD_GELU, TRAIN>), g, b, 0, c->stream, n, in3, c->wp[0],
+                     c->p + off_b(0), nullptr, c->z[0], nullptr, c->a[0]);
+  for (int l = 1; l < 3; ++l)
+    hipLaunchKernelGGL((k_conv<16, C_FWD_GELU, TRAIN>), g, b, 0, c->stream, n, c->a[l - 1],
+                       c->wp[l], c->p + off_b(l), nullptr, c->z[l], nullptr, c->a[l]);
+  // last layer: bias padded to 16 channels (a device copy past the gradient)
+  hipLaunchKernelGGL((k_conv<16, C_FWD_LAST, TRAIN>), g, b, 0, c->stream, n, c->a[2], c->wp[3],
+                     c->g + off_pad(), nullptr, TRAIN ? c->z[3] : mu, logvar, nullptr);
   CCHK(c, hipGetLastError());
   return HMC_OK;
 }
 // forward for training (keeps the pre-activations) and for inference
-hmc_status forward(cnn_ctx* c, int n, const float* in3) { return forward_t<true>(c, n, in3); }
-hmc_status infer(cnn_ctx* c, int n, const float* in3) {
+hmc_status forward(cnn_ctx* c, int n, const float* in3) {
+  return forward_t<true>(c, n, in3, nullptr, nullptr);
+}
+hmc_status infer(cnn_ctx* c, int n, const float* in3, float* mu, float* logvar) {
   c->grad_valid = false;  // overwrites the activations of the last gradient evaluation
-  return forward_t<false>(c, n, in3);
+  return forward_t<false>(c, n, in3, mu, logvar);
 }
 
 hmc_status gradient(cnn_ctx* c, int n, const float* in3, const float* target, double* loss) {
@@ -578,9 +588,8 @@ hmc_status gradient(cnn_ctx* c, int n, const float* in3, const float* target, do
   hmc_status st = forward(c, n, in3);
   if (st != HMC_OK) return st;
   const long long nv = (long long)n * n * n;
-  const int blocks = (int)((nv / 16 + 3) / 4);
-  hipLaunchKernelGGL(k_loss, dim3(1024), dim3(256), 0, c->stream, nv, c->z[3], target, c->dz[3],
-                     c->lpart);
+  hipLaunchKernelGGL(k_loss, dim3(1024), dim3(256), 0, c->stream, nv, (const float2*)c->z[3], target,
+                     (uint4*)c->dz[3], c->lpart);
   const long long nchunks = nv / 16;
   const bool lds = n % kBZ == 0;
   const int nbricks = lds ? (n / kBX) * (n / kBY) * (n / kBZ) : 0;
@@ -605,15 +614,9 @@ hmc_status gradient(cnn_ctx* c, int n, const float* in3, const float* target, do
                          c->wpart, c->dbpart);
     hipLaunchKernelGGL(k_wreduce, dim3(kRedBlocks + 1), dim3(1024), 0, c->stream, c->wpart,
                        c->dbpart, nw, kCin[l], kCout[l], c->g + off_w(l), c->g + off_b(l));
-    if (l > 0) {
-      if (n % kBZ == 0)
-        hipLaunchKernelGGL((k_conv_lds<C_DGRAD, true>), dim3((n / kBX) * (n / kBY) * (n / kBZ)),
-                           dim3(256), 0, c->stream, n, dz, c->wd[l], nullptr, c->z[l - 1],
-                           nullptr, c->dz[l - 1]);
-      else
-        hipLaunchKernelGGL((k_conv<16, C_DGRAD, 27, true>), dim3(blocks), dim3(256), 0,
-                           c->stream, n, dz, c->wd[l], nullptr, c->z[l - 1], nullptr, c->dz[l - 1]);
-    }
+    if (l > 0)
+      hipLaunchKernelGGL((k_conv<16, C_DGRAD, true>), dim3(conv_bricks(n)), dim3(256), 0, c->stream,
+                         n, dz, c->wd[l], nullptr, c->z[l - 1], nullptr, nullptr, c->dz[l - 1]);
   }
   CCHK(c, hipGetLastError());
   CCHK(c, hipMemcpyAsync(c->lpart_h, c->lpart, 1024 * sizeof(double), hipMemcpyDeviceToHost,
@@ -667,7 +670,7 @@ hmc_status cnn_create(const float* params, void* stream, cnn_ctx** out) {
   hipError_t e;
   // g holds the gradient and, past its end, the last layer's bias padded to 16
   if ((e = hipMalloc(&c->p, np * sizeof(float))) != hipSuccess) return bail("hipMalloc", e);
-  if ((e = hipMalloc(&c->g, (np + 16) * sizeof(float))) != hipSuccess) return bail("hipMalloc", e);
+  if ((e = hipMalloc(&c->g, n_grad() * sizeof(float))) != hipSuccess) return bail("hipMalloc", e);
   if ((e = hipMalloc(&c->m1, np * sizeof(float))) != hipSuccess) return bail("hipMalloc", e);
   if ((e = hipMalloc(&c->m2, np * sizeof(float))) != hipSuccess) return bail("hipMalloc", e);
   for (int l = 0; l < 4; ++l) {
@@ -682,15 +685,15 @@ hmc_status cnn_create(const float* params, void* stream, cnn_ctx** out) {
   if ((e = hipMalloc(&c->lpart, 1024 * sizeof(double))) != hipSuccess) return bail("hipMalloc", e);
   if ((e = hipHostMalloc((void**)&c->lpart_h, 1024 * sizeof(double), 0)) != hipSuccess)
     return bail("hipHostMalloc", e);
-  std::vector<float> zeros(np + 16, 0.f);
+  std::vector<float> zeros(n_grad(), 0.f);
   if ((e = hipMemcpy(c->p, params, np * sizeof(float), hipMemcpyHostToDevice)) != hipSuccess)
     return bail("upload", e);
   if ((e = hipMemcpy(c->m1, zeros.data(), np * sizeof(float), hipMemcpyHostToDevice)) != hipSuccess ||
       (e = hipMemcpy(c->m2, zeros.data(), np * sizeof(float), hipMemcpyHostToDevice)) != hipSuccess ||
-      (e = hipMemcpy(c->g, zeros.data(), (np + 16) * sizeof(float), hipMemcpyHostToDevice)) != hipSuccess)
+      (e = hipMemcpy(c->g, zeros.data(), n_grad() * sizeof(float), hipMemcpyHostToDevice)) != hipSuccess)
     return bail("upload", e);
   // padded last-layer bias after the gradient
-  if ((e = hipMemcpy(c->g + np, params + off_b(3), 2 * sizeof(float), hipMemcpyHostToDevice)) != hipSuccess)
+  if ((e = hipMemcpy(c->g + off_pad(), params + off_b(3), 2 * sizeof(float), hipMemcpyHostToDevice)) != hipSuccess)
     return bail("upload", e);
   if (pack_all(c) != HMC_OK) {
     g_cerr = c->err;
@@ -712,11 +715,7 @@ hmc_status cnn_forward(cnn_ctx* c, int32_t n, const float* in3, float* mu, float
   if (!c || !in3) return cfail(c, HMC_EINVAL, "null argument");
   hmc_status st = ensure(c, n);
   if (st != HMC_OK) return st;
-  if ((st = infer(c, n, in3)) != HMC_OK) return st;
-  const long long nv = (long long)n * n * n;
-  hipLaunchKernelGGL(k_outputs, dim3(4096), dim3(256), 0, c->stream, nv, c->z[3], mu, logvar);
-  CCHK(c, hipGetLastError());
-  return HMC_OK;
+  return infer(c, n, in3, mu, logvar);
 }
 
 hmc_status cnn_features(cnn_ctx* c, int32_t n, const float* beta, float beta_scale,
@@ -747,7 +746,7 @@ hmc_status cnn_layer_state(cnn_ctx* c, int32_t layer, float* z, float* a, float*
   if (c->n == 0 || !c->grad_valid) return cfail(c, HMC_EINVAL, "no cnn_gradient or cnn_train_step yet");
   const long long nv = (long long)c->n * c->n * c->n;
   hipLaunchKernelGGL(k_layer_state, dim3(4096), dim3(256), 0, c->stream, nv, kCout[layer],
-                     c->z[layer], layer < 3 ? c->a[layer] : nullptr, c->dz[layer], z, a, dz);
+                     layer < 3 ? 16 : 2, c->z[layer], layer < 3 ? c->a[layer] : nullptr, c->dz[layer], z, a, dz);
   CCHK(c, hipGetLastError());
   return HMC_OK;
 }
@@ -764,7 +763,7 @@ hmc_status cnn_train_step(cnn_ctx* c, int32_t n, const float* in3, const float* 
   hipLaunchKernelGGL(k_adam, dim3((np + 255) / 256), dim3(256), 0, c->stream, np, c->p, c->g, c->m1,
                      c->m2, lr, c1, c2);
   // keep the padded last-layer bias in step with the master copy
-  CCHK(c, hipMemcpyAsync(c->g + np, c->p + off_b(3), 2 * sizeof(float), hipMemcpyDeviceToDevice,
+  CCHK(c, hipMemcpyAsync(c->g + off_pad(), c->p + off_b(3), 2 * sizeof(float), hipMemcpyDeviceToDevice,
                          c->stream));
   return pack_all(c);
 }
