@@ -56,6 +56,83 @@ __device__ __forceinline__ float gelu_grad(float z) {
   return norm_cdf(z) + z * expf(-0.5f * z * z) * 0.3989422804014327f;
 }
 
+// The same GELU and GELU' values rounded to bf16, four at a time and bit for bit, without
+// erfcf where the rounding does not need its last digits.  With y = |z| and t = 1 / (1 + 0.3 y),
+//   Phi(-y) = exp(-y^2 / 2) t P(t),
+// P the degree-7 polynomial with the smallest relative error on 0 <= y <= 10.5 (5.0e-8; a
+// weighted least-squares fit iterated towards equal ripples).  Evaluated in float32 the value is
+// within kErr0 + kErr1 y^2 (relative; for GELU' times the magnitudes of the two terms it
+// adds) of the erfcf form above; where no bf16 rounding boundary lies within that distance,
+// both round to the same bf16 value, else (about one value in 1300), and outside the range of
+// the bound (y >= 10, tiny, huge or not finite), the erfcf form decides.  Checked against it for
+// every float32 z: the largest deviation is two thirds of the bound.  erfcf is about 50
+// instructions, three of them quarter rate, and at 256^3 a layer evaluates it 268 million
+// times: a hidden layer went from 713 to 615 us and the first from 511 to 372 us.
+constexpr float kErr0 = 9e-7f, kErr1 = 3.75e-7f;
+struct Cdf {
+  float phi, e, err;  // Phi(z), exp(-z^2 / 2), the relative bound
+  bool ok;
+};
+__device__ __forceinline__ Cdf norm_cdf_short(float z) {
+  const float y = fabsf(z), t = __builtin_amdgcn_rcpf(__builtin_fmaf(0.3f, y, 1.f)), y2 = y * y;
+  float p = 0.037548013f;
+  p = __builtin_fmaf(p, t, -0.165077418f);
+  p = __builtin_fmaf(p, t, 0.220085055f);
+  p = __builtin_fmaf(p, t, -0.0665243194f);
+  p = __builtin_fmaf(p, t, 0.135496393f);
+  p = __builtin_fmaf(p, t, 0.097756058f);
+  p = __builtin_fmaf(p, t, 0.121111214f);
+  p = __builtin_fmaf(p, t, 0.119605042f);
+  Cdf c;
+  c.e = __builtin_amdgcn_exp2f(-0.721347520444481704f * y2);
+  const float q = c.e * (t * p);
+  c.phi = z > 0.f ? 1.f - q : q;
+  c.err = __builtin_fmaf(kErr1, y2, kErr0);
+  c.ok = y2 < 100.f;
+  return c;
+}
+// true if r - b and r + b (b >= 0) round to the same bf16 value
+__device__ __forceinline__ bool same_bf(float r, float b) {
+  return ((__float_as_uint(r - b) + 0x8000u) ^ (__float_as_uint(r + b) + 0x8000u)) < 0x10000u;
+}
+__device__ __forceinline__ bool plain(float r) { return fabsf(r) > 1e-30f && fabsf(r) < 1e30f; }
+
+__device__ __forceinline__ ushort4 gelu_bf4(const float* z) {
+  uint16_t o[4];
+  bool ok[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const Cdf c = norm_cdf_short(z[i]);
+    const float r = z[i] * c.phi;
+    ok[i] = c.ok && plain(r) && same_bf(r, fabsf(r) * c.err);
+    o[i] = (uint16_t)((__float_as_uint(r) + 0x8000u) >> 16);
+  }
+  if (!(ok[0] && ok[1] && ok[2] && ok[3])) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (!ok[i]) o[i] = f2bf(gelu(z[i]));
+  }
+  return make_ushort4(o[0], o[1], o[2], o[3]);
+}
+// v gelu'(z)
+__device__ __forceinline__ ushort4 gelu_grad_bf4(const float* v, const float* z) {
+  uint16_t o[4];
+  bool ok[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const Cdf c = norm_cdf_short(z[i]);
+    const float zp = z[i] * (c.e * 0.3989422804014327f), r = v[i] * (c.phi + zp);
+    ok[i] = c.ok && plain(r) && same_bf(r, fabsf(v[i]) * (c.err * (c.phi + fabsf(zp))));
+    o[i] = (uint16_t)((__float_as_uint(r) + 0x8000u) >> 16);
+  }
+  if (!(ok[0] && ok[1] && ok[2] && ok[3])) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (!ok[i]) o[i] = f2bf(v[i] * gelu_grad(z[i]));
+  }
+  return make_ushort4(o[0], o[1], o[2], o[3]);
+}
+
 // ------------------------------------------------------------------ kernels
 // in3 float [3][V] -> bf16 [V][4] (4th channel zero)
 __global__ void __launch_bounds__(256) k_input(long long nv, const float* __restrict__ in3,
@@ -111,8 +188,8 @@ __device__ __forceinline__ int brick_of(int b, int g) {
 // 90 reads for 216 MFMAs, where one read per MFMA kept LDS as busy as the matrix cores.
 // The order of the products of one output is that of the taps, whatever the brick.
 // What bounds it at 256^3 (kernel trace): the products and the staging (396 us for the
-// last layer) and, for the hidden layers, erfc and the stores (713 us; 763 before, and the
-// last layer 661 us plus 257 us to pick its two channels out of 16 stored ones).
+// last layer) and, for the hidden layers, GELU and the stores (615 us; 763 before this form
+// and gelu_bf4, and the last layer 661 us plus 257 us to pick its two channels out of 16).
 // TRAIN: keep the pre-activation for the backward pass.  LAST: out0, out1 are the two
 // output channels, or out0 the pairs [V][2] for the loss (TRAIN).
 template <int CS, int MODE, bool TRAIN>
@@ -200,25 +277,23 @@ __global__ void __launch_bounds__(256, 4) k_conv(int n, const void* __restrict__
   for (int r = 0; r < kCY; ++r) {
     if (y0 + r >= n || zz >= n) continue;
     const long long v = ((long long)(x0 + wave) * n + y0 + r) * n + zz;
-    const float4 val = make_float4(acc[r][0] + bi.x, acc[r][1] + bi.y, acc[r][2] + bi.z, acc[r][3] + bi.w);
+    const float val[4] = {acc[r][0] + bi.x, acc[r][1] + bi.y, acc[r][2] + bi.z, acc[r][3] + bi.w};
     if constexpr (MODE == C_FWD_GELU) {
-      if (TRAIN) reinterpret_cast<float4*>(out0)[v * 4 + grp] = val;
-      reinterpret_cast<ushort4*>(aout)[v * 4 + grp] =
-          make_ushort4(f2bf(gelu(val.x)), f2bf(gelu(val.y)), f2bf(gelu(val.z)), f2bf(gelu(val.w)));
+      if (TRAIN) reinterpret_cast<float4*>(out0)[v * 4 + grp] = make_float4(val[0], val[1], val[2], val[3]);
+      reinterpret_cast<ushort4*>(aout)[v * 4 + grp] = gelu_bf4(val);
     } else if constexpr (MODE == C_FWD_LAST) {
       if (grp == 0) {  // channels 0, 1
         if (TRAIN) {
-          reinterpret_cast<float2*>(out0)[v] = make_float2(val.x, val.y);
+          reinterpret_cast<float2*>(out0)[v] = make_float2(val[0], val[1]);
         } else {
-          if (out0) out0[v] = val.x;
-          if (out1) out1[v] = val.y;
+          if (out0) out0[v] = val[0];
+          if (out1) out1[v] = val[1];
         }
       }
     } else {
-      const float4 zp = reinterpret_cast<const float4*>(zprev)[v * 4 + grp];
-      reinterpret_cast<ushort4*>(aout)[v * 4 + grp] =
-          make_ushort4(f2bf(acc[r][0] * gelu_grad(zp.x)), f2bf(acc[r][1] * gelu_grad(zp.y)),
-                       f2bf(acc[r][2] * gelu_grad(zp.z)), f2bf(acc[r][3] * gelu_grad(zp.w)));
+      const float4 zv = reinterpret_cast<const float4*>(zprev)[v * 4 + grp];
+      const float da[4] = {acc[r][0], acc[r][1], acc[r][2], acc[r][3]}, zp[4] = {zv.x, zv.y, zv.z, zv.w};
+      reinterpret_cast<ushort4*>(aout)[v * 4 + grp] = gelu_grad_bf4(da, zp);
     }
   }
 }
