@@ -11,7 +11,7 @@
 // Backward: the input gradient is the same convolution of the output gradient
 // with mirrored taps and transposed weights, fused with GELU'(z); the weight
 // gradient runs the MFMA with K over voxels (A = activations gathered per tap,
-// B = output gradient), one partial per wave, summed in a fixed order.
+// B = output gradient), one partial per block, summed in a fixed order.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -29,7 +29,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kCin[4] = {3, 16, 16, 16};
 constexpr int kCout[4] = {16, 16, 16, 2};
-constexpr int kWaves = 2048;  // weight-gradient partials (one per wave)
+constexpr int kTile = 27 * 256;  // entries of one weight-gradient partial
 
 inline int off_w(int l) {
   int o = 0;
@@ -134,19 +134,6 @@ __device__ __forceinline__ ushort4 gelu_grad_bf4(const float* v, const float* z)
 }
 
 // ------------------------------------------------------------------ kernels
-// in3 float [3][V] -> bf16 [V][4] (4th channel zero)
-__global__ void __launch_bounds__(256) k_input(long long nv, const float* __restrict__ in3,
-                                               uint16_t* __restrict__ a0) {
-  for (long long v = (long long)blockIdx.x * 256 + threadIdx.x; v < nv; v += (long long)gridDim.x * 256) {
-    ushort4 o;
-    o.x = f2bf(in3[v]);
-    o.y = f2bf(in3[nv + v]);
-    o.z = f2bf(in3[2 * nv + v]);
-    o.w = 0;
-    reinterpret_cast<ushort4*>(a0)[v] = o;
-  }
-}
-
 __global__ void __launch_bounds__(256) k_features(long long nv, const float* __restrict__ beta,
                                                   float scale, const float* __restrict__ mask,
                                                   const float* __restrict__ sel,
@@ -298,10 +285,6 @@ __global__ void __launch_bounds__(256, 4) k_conv(int n, const void* __restrict__
   }
 }
 
-constexpr int kBX = 2, kBY = 8;  // brick of the weight gradient
-constexpr int kHX = kBX + 2, kHY = kBY + 2;
-constexpr int kHalo = kHX * kHY * kHZ;
-
 // Gaussian NLL per voxel; writes the bf16 output gradient [V][16] and block partials.
 __global__ void __launch_bounds__(256) k_loss(long long nv, const float2* __restrict__ z4,
                                               const float* __restrict__ target,
@@ -324,141 +307,170 @@ __global__ void __launch_bounds__(256) k_loss(long long nv, const float2* __rest
   if (threadIdx.x == 0) part[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 
-// Weight gradient: dW[t][ci][co] = sum_v a[v + d_t][ci] dz[v][co]; one partial per wave.
-template <int CS>
-__global__ void __launch_bounds__(256) k_wgrad(int n, const uint16_t* __restrict__ a,
-                                               const uint16_t* __restrict__ dz, int cpw,
-                                               float* __restrict__ part, float* __restrict__ dbpart) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const long long nv = (long long)n * n * n;
-  const long long nchunks = nv / 16;
-  const int gw = blockIdx.x * 4 + wave;
-  const int m = lane & 15, grp = lane >> 4;
-  f32x4 acc[27];
-#pragma unroll
-  for (int t = 0; t < 27; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float db = 0.f;
-  const long long c0 = (long long)gw * cpw;
-  const long long c1 = c0 + cpw < nchunks ? c0 + cpw : nchunks;
-  for (long long c = c0; c < c1; ++c) {
-    int xs[4], ys[4], zs[4];
-    bf16x4 b;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const long long v = c * 16 + 4 * grp + i;
-      xs[i] = (int)(v / ((long long)n * n));
-      ys[i] = (int)((v / n) % n);
-      zs[i] = (int)(v % n);
-      const uint16_t g = dz[v * 16 + m];
-      b[i] = (short)g;
-      db += bf2f(g);
-    }
-#pragma unroll
-    for (int t = 0; t < 27; ++t) {
-      bf16x4 av = {0, 0, 0, 0};
-      if (m < CS) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int xx = xs[i] + t / 9 - 1, yy = ys[i] + (t / 3) % 3 - 1, zz = zs[i] + t % 3 - 1;
-          if ((unsigned)xx < (unsigned)n && (unsigned)yy < (unsigned)n && (unsigned)zz < (unsigned)n)
-            av[i] = (short)a[(((long long)xx * n + yy) * n + zz) * CS + m];
-        }
-      }
-      acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, b, acc[t], 0, 0, 0);
-    }
-  }
-  float* o = part + (size_t)gw * 27 * 256;
-#pragma unroll
-  for (int t = 0; t < 27; ++t)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) o[(t * 16 + 4 * grp + i) * 16 + m] = acc[t][i];
-  db += __shfl_xor(db, 16);
-  db += __shfl_xor(db, 32);
-  if (lane < 16) dbpart[gw * 16 + lane] = db;
+// Weight gradient: dW[t][ci][co] = sum_v a[v + d_t][ci] dz[v][co], the MFMA's K over 16
+// voxels of a z row (B = dz, columns co).  A block walks bricks of BX x BY x 16 voxels and
+// stages them channel-major in LDS, the activations with their halo; a staging thread turns
+// 4 voxels x 4 channels (8-byte loads and LDS writes).  The channel pitches are 8 mod 64
+// words, so that a fragment read (16 channels x 4 voxel quads) meets every bank twice, its
+// minimum.  Wave w owns 4 rows; an input row is read once (an aligned quad and the two voxels
+// after it) and gives the fragments of all three z shifts in registers for every row of the
+// wave it is a neighbour of: 36 reads for 108 MFMAs, where each fragment took four 2-byte
+// reads.  CS = 16: A rows are the input channels of one tap.  CS = 4: A rows are (z shift,
+// channel), 9 MFMAs a row instead of 27, read from the network's float32 input.  The
+// waves' sums meet in LDS, one partial per block, summed by k_wreduce in a fixed order.
+// 128^3: 74 us a 16-channel layer and 68 us for the first (103 and 202 us before); the
+// accumulators (108 registers) leave 3 blocks per compute unit.
+constexpr int kBX = 2, kBY = 8;
+constexpr int kHX = kBX + 2, kHY = kBY + 2, kRowP = 20;  // halo rows hold 18 voxels of 20
+constexpr int kChA = kHX * kHY * kRowP + 16, kChD = kBX * kBY * kBZ + 16;  // channel pitches
+static_assert(kChA / 2 % 64 == 24 && kChD / 2 % 64 == 8 && kChA % 4 == 0, "channel pitches");
+
+// 4 channels of 4 voxels -> 4 voxels of 4 channels
+__device__ __forceinline__ void turn4(const uint2* v, uint2* c) {
+  c[0] = make_uint2((v[0].x & 0xffffu) | v[1].x << 16, (v[2].x & 0xffffu) | v[3].x << 16);
+  c[1] = make_uint2(v[0].x >> 16 | (v[1].x & 0xffff0000u), v[2].x >> 16 | (v[3].x & 0xffff0000u));
+  c[2] = make_uint2((v[0].y & 0xffffu) | v[1].y << 16, (v[2].y & 0xffffu) | v[3].y << 16);
+  c[3] = make_uint2(v[0].y >> 16 | (v[1].y & 0xffff0000u), v[2].y >> 16 | (v[3].y & 0xffff0000u));
 }
 
-// Weight gradient with bricks staged in LDS, channel-major: the block walks
-// bricks of BX x BY x 16 voxels; per brick it stages the haloed activations
-// a[ci][voxel] and the output gradient dz[co][voxel], and each wave runs four
-// K-steps (one 16-voxel z-row each) for all 27 taps, accumulating one partial
-// per wave (A = shifted activations, rows ci; B = dz, columns co).
+__host__ __device__ inline int wgrad_bricks(int n) {
+  return (n / kBX) * ((n + kBY - 1) / kBY) * ((n + kBZ - 1) / kBZ);
+}
+
 template <int CS>
-__global__ void __launch_bounds__(256) k_wgrad_lds(int n, const uint16_t* __restrict__ a,
-                                                   const uint16_t* __restrict__ dz,
-                                                   float* __restrict__ part,
-                                                   float* __restrict__ dbpart) {
-  constexpr int kBV = kBX * kBY * kBZ;
-  static_assert(kBV == 256 && kBX * kBY == 16, "one brick voxel per thread, four rows per wave");
-  __shared__ uint16_t sa[CS][kHalo];
-  __shared__ uint16_t sd[16][kBV];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+__global__ void __launch_bounds__(256, 3) k_wgrad(int n, const void* __restrict__ in,
+                                               const uint16_t* __restrict__ dz,
+                                               float* __restrict__ part, float* __restrict__ dbpart) {
+  constexpr int kT = CS == 16 ? 27 : 9;  // accumulator tiles
+  constexpr int kLds = (CS == 16 ? 16 : 3) * kChA + 16 * kChD;
+  static_assert(kBX * kBY == 16 && 2 * kLds >= 4 * kT * 256, "rows per wave; reduction buffer");
+  __shared__ __align__(16) uint16_t lds[kLds];
+  __shared__ float sdb[4][16];
+  uint16_t* const sa = lds;
+  uint16_t* const sd = lds + (CS == 16 ? 16 : 3) * kChA;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int m = lane & 15, grp = lane >> 4;
-  const int nbz = n / kBZ, nby = n / kBY;
-  const int nbricks = (n / kBX) * nby * nbz;
-  f32x4 acc[27];
+  const int nbz = (n + kBZ - 1) / kBZ, nby = (n + kBY - 1) / kBY, nbricks = wgrad_bricks(n);
+  const long long nv = (long long)n * n * n;
+  f32x4 acc[kT];
 #pragma unroll
-  for (int t = 0; t < 27; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int t = 0; t < kT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
   float db = 0.f;
   for (int brick = blockIdx.x; brick < nbricks; brick += gridDim.x) {
-    const int bz = brick % nbz, by = (brick / nbz) % nby, bx = brick / (nbz * nby);
-    const int x0 = bx * kBX, y0 = by * kBY, z0 = bz * kBZ;
+    const int x0 = brick / (nbz * nby) * kBX, y0 = brick / nbz % nby * kBY, z0 = brick % nbz * kBZ;
     __syncthreads();  // the previous brick's reads are done
-    for (int vox = threadIdx.x; vox < kHalo; vox += 256) {
-      const int hz = vox % kHZ, hy = (vox / kHZ) % kHY, hx = vox / (kHZ * kHY);
-      const int xx = x0 + hx - 1, yy = y0 + hy - 1, zz = z0 + hz - 1;
-      if ((unsigned)xx < (unsigned)n && (unsigned)yy < (unsigned)n && (unsigned)zz < (unsigned)n) {
-        const uint16_t* src = a + (((long long)xx * n + yy) * n + zz) * CS;
+    if constexpr (CS == 16) {
+      for (int i = tid; i < kHX * kHY * 5 * 4; i += 256) {
+        const int cg = i & 3, q = (i >> 2) % 5, row = i / 20;
+        const int xx = x0 + row / kHY - 1, yy = y0 + row % kHY - 1, zb = z0 + 4 * q - 1;
+        const bool okr = (unsigned)xx < (unsigned)n && (unsigned)yy < (unsigned)n;
+        const uint2* src = reinterpret_cast<const uint2*>(in) + (((long long)xx * n + yy) * n + zb) * 4 + cg;
+        uint2 v[4], c[4];
 #pragma unroll
-        for (int ch = 0; ch < CS; ++ch) sa[ch][vox] = src[ch];
-      } else {
+        for (int j = 0; j < 4; ++j)
+          v[j] = okr && (unsigned)(zb + j) < (unsigned)n && 4 * q + j < kHZ ? src[4 * j] : make_uint2(0u, 0u);
+        turn4(v, c);
 #pragma unroll
-        for (int ch = 0; ch < CS; ++ch) sa[ch][vox] = 0;
+        for (int j = 0; j < 4; ++j)
+          *reinterpret_cast<uint2*>(sa + (4 * cg + j) * kChA + row * kRowP + 4 * q) = c[j];
+      }
+    } else {
+      for (int i = tid; i < kHX * kHY * 5 * 3; i += 256) {
+        const int q = i % 5, row = i / 5 % (kHX * kHY), ch = i / (5 * kHX * kHY);
+        const int xx = x0 + row / kHY - 1, yy = y0 + row % kHY - 1, zb = z0 + 4 * q - 1;
+        const bool okr = (unsigned)xx < (unsigned)n && (unsigned)yy < (unsigned)n;
+        const float* src = reinterpret_cast<const float*>(in) + ch * nv + ((long long)xx * n + yy) * n + zb;
+        uint32_t v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          v[j] = okr && (unsigned)(zb + j) < (unsigned)n && 4 * q + j < kHZ ? f2bf(src[j]) : 0u;
+        *reinterpret_cast<uint2*>(sa + ch * kChA + row * kRowP + 4 * q) = make_uint2(v[0] | v[1] << 16, v[2] | v[3] << 16);
       }
     }
-    {
-      const int v = threadIdx.x;  // kBV == 256 voxels of the brick, one per thread
-      const int vz = v % kBZ, vy = (v / kBZ) % kBY, vx = v / (kBZ * kBY);
-      const uint4* src = reinterpret_cast<const uint4*>(
-          dz + (((long long)(x0 + vx) * n + (y0 + vy)) * n + (z0 + vz)) * 16);
-      const uint4 lo = src[0], hi = src[1];
-      const uint32_t wds[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+    {  // one 4 x 4 block of dz per thread
+      const int cg = tid & 3, q = (tid >> 2) & 3, row = tid >> 4;
+      const int yy = y0 + row % kBY, zb = z0 + 4 * q;
+      const uint2* src = reinterpret_cast<const uint2*>(dz) + (((long long)(x0 + row / kBY) * n + yy) * n + zb) * 4 + cg;
+      uint2 v[4], c[4];
 #pragma unroll
-      for (int ch = 0; ch < 16; ++ch)
-        sd[ch][v] = (uint16_t)(ch & 1 ? wds[ch >> 1] >> 16 : wds[ch >> 1] & 0xffffu);
+      for (int j = 0; j < 4; ++j) v[j] = yy < n && zb < n ? src[4 * j] : make_uint2(0u, 0u);  // n % 4 == 0
+      turn4(v, c);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) *reinterpret_cast<uint2*>(sd + (4 * cg + j) * kChD + row * kBZ + 4 * q) = c[j];
     }
     __syncthreads();
+    const int rx = wave >> 1, ry0 = (wave & 1) * 4;
+    bf16x4 b[4];
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const int row = wave * 4 + ks;  // (x, y) row of the brick, 16 voxels along z
-      const int rx = row / kBY, ry = row % kBY;
-      const bf16x4 b = *reinterpret_cast<const bf16x4*>(&sd[m][row * kBZ + 4 * grp]);
+    for (int r = 0; r < 4; ++r) {
+      b[r] = *reinterpret_cast<const bf16x4*>(sd + m * kChD + (wave * 4 + r) * kBZ + 4 * grp);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) db += bf2f((uint16_t)b[i]);
-#pragma unroll
-      for (int t = 0; t < 27; ++t) {
-        const int hx = rx + t / 9, hy = ry + (t / 3) % 3, hz0 = 4 * grp + t % 3;
-        bf16x4 av = {0, 0, 0, 0};
-        if (m < CS) {
-          const uint16_t* p = &sa[m < CS ? m : 0][(hx * kHY + hy) * kHZ + hz0];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) av[i] = (short)p[i];
-        }
-        acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(av, b, acc[t], 0, 0, 0);
-      }
+      for (int i = 0; i < 4; ++i) db += bf2f((uint16_t)b[r][i]);
     }
+    const uint16_t* sm = sa + (CS == 16 ? m : (m & 3) < 3 ? m & 3 : 2) * kChA + 4 * grp;
+#pragma unroll
+    for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+      for (int h = 0; h < 6; ++h) {
+        const uint16_t* p = sm + ((rx + dx) * kHY + ry0 + h) * kRowP;
+        const uint2 lo = *reinterpret_cast<const uint2*>(p);
+        const uint32_t hi = *reinterpret_cast<const uint32_t*>(p + 4);
+        uint2 f[3];  // z shifts 0, 1, 2
+        f[0] = lo;
+        f[1] = make_uint2(__builtin_amdgcn_alignbit(lo.y, lo.x, 16), __builtin_amdgcn_alignbit(hi, lo.y, 16));
+        f[2] = make_uint2(lo.y, hi);
+        if constexpr (CS == 16) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (r <= h && h <= r + 2)
+#pragma unroll
+              for (int s = 0; s < 3; ++s) {
+                const int t = (dx * 3 + h - r) * 3 + s;
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(bf16x4, f[s]), b[r], acc[t], 0, 0, 0);
+              }
+        } else {
+          const int s = m >> 2;  // 3: rows of no tap, their sums are not read
+          const uint2 g = s == 0 ? f[0] : s == 1 ? f[1] : f[2];
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (r <= h && h <= r + 2) {
+              const int t = dx * 3 + h - r;
+              acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(bf16x4, g), b[r], acc[t], 0, 0, 0);
+            }
+        }
+      }
   }
-  const int gw = blockIdx.x * 4 + wave;
-  float* o = part + (size_t)gw * 27 * 256;
-#pragma unroll
-  for (int t = 0; t < 27; ++t)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) o[(t * 16 + 4 * grp + i) * 16 + m] = acc[t][i];
+  // the four waves' sums, in wave order
   db += __shfl_xor(db, 16);
   db += __shfl_xor(db, 32);
-  if (lane < 16) dbpart[gw * 16 + lane] = db;
+  if (lane < 16) sdb[wave][lane] = db;
+  float* const red = reinterpret_cast<float*>(lds);
+  for (int w = 0; w < 4; ++w) {
+    __syncthreads();
+    if (wave == w)
+#pragma unroll
+      for (int t = 0; t < kT; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          float* o = red + t * 256 + (4 * grp + i) * 16 + m;
+          *o = w == 0 ? acc[t][i] : *o + acc[t][i];
+        }
+  }
+  __syncthreads();
+  float* o = part + (size_t)blockIdx.x * kTile;
+  if constexpr (CS == 16) {
+    for (int i = tid; i < kTile; i += 256) o[i] = red[i];
+  } else {  // rows (z shift, channel) of (dx, dy) -> rows of tap 3 (dx, dy) + z shift
+    for (int i = tid; i < kT * 192; i += 256) {
+      const int t = i / 192, row = i / 16 % 12, co = i & 15;
+      o[((t * 3 + row / 4) * 16 + row % 4) * 16 + co] = red[t * 256 + row * 16 + co];
+    }
+  }
+  if (tid < 16) dbpart[blockIdx.x * 16 + tid] = ((sdb[0][tid] + sdb[1][tid]) + sdb[2][tid]) + sdb[3][tid];
 }
 
-// One layer's stored state in float32, [V][cout]: pre-activations (rows of zs), bf16 activations and bf16 pre-activation gradients (either pointer may be null).
+// One layer's stored state in float32, [V][cout]: pre-activations (rows of zs), bf16
+// activations and bf16 pre-activation gradients (either pointer may be null).
 __global__ void __launch_bounds__(256) k_layer_state(long long nv, int cout, int zs,
                                                      const float* __restrict__ z16,
                                                      const uint16_t* __restrict__ a16,
@@ -474,15 +486,13 @@ __global__ void __launch_bounds__(256) k_layer_state(long long nv, int cout, int
   }
 }
 
-// Sum the per-wave partials of one layer into the flat gradient.  A block takes 64
+// Sum the per-block partials of one layer into the flat gradient.  A block takes 64
 // consecutive entries of the [27][16][16] partial tile and splits the partials over its
 // 16 waves (wave s: partials s, s + 16, ...), whose sums it adds in wave order, so the
 // order is fixed; the block past the tile does the same for the 16 bias sums.  Reading
-// the partials is the bound (2048 x 27.6 KB = 56.6 MB at 128^3): a thread that walked
+// the partials is the bound (768 x 27.6 KB = 21 MB at 128^3: 5.2 us); a thread that walked
 // all partials of one entry by itself had one dependent add per 27.6 KB of stride and
-// 27 blocks in flight (767 us a layer); split this way the 128^3 training step, which
-// reduces four layers, went from 4110 to 1352 us.
-constexpr int kTile = 27 * 256;        // entries of one partial
+// 27 blocks in flight (767 us a layer with 2048 partials).
 constexpr int kRedBlocks = kTile / 64;  // and one block more for the biases
 __global__ void __launch_bounds__(1024) k_wreduce(const float* __restrict__ part,
                                                   const float* __restrict__ dbpart, int nw, int cin,
@@ -559,6 +569,7 @@ using namespace cnnk;
 
 struct cnn_ctx {
   hipStream_t stream = nullptr;
+  int parts = 0;  // weight-gradient partials: 3 blocks per compute unit
   std::string err;
   float *p = nullptr, *g = nullptr, *m1 = nullptr, *m2 = nullptr;
   bf16x4* wp[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -568,7 +579,7 @@ struct cnn_ctx {
   bool grad_valid = false;  // the stored pre-activations and gradients belong to the last
                             // cnn_gradient / cnn_train_step
   // activations for the current N
-  uint16_t *a0 = nullptr, *a[3] = {nullptr, nullptr, nullptr};
+  uint16_t* a[3] = {nullptr, nullptr, nullptr};
   // bf16 gradient of the loss with respect to each layer's pre-activations, one
   // buffer per layer so that the last backward pass can be inspected
   uint16_t* dz[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -608,11 +619,9 @@ hmc_status pack_all(cnn_ctx* c) {
 }
 
 void free_acts(cnn_ctx* c) {
-  (void)hipFree(c->a0);
   for (int i = 0; i < 3; ++i) (void)hipFree(c->a[i]);
   for (int i = 0; i < 4; ++i) (void)hipFree(c->z[i]);
   for (int i = 0; i < 4; ++i) (void)hipFree(c->dz[i]);
-  c->a0 = nullptr;
   for (int i = 0; i < 4; ++i) c->dz[i] = nullptr;
   for (int i = 0; i < 3; ++i) c->a[i] = nullptr;
   for (int i = 0; i < 4; ++i) c->z[i] = nullptr;
@@ -624,7 +633,6 @@ hmc_status ensure(cnn_ctx* c, int n) {
   if (c->n == n) return HMC_OK;
   free_acts(c);
   const size_t nv = (size_t)n * n * n;
-  CCHK(c, hipMalloc(&c->a0, nv * 4 * sizeof(uint16_t)));
   for (int i = 0; i < 3; ++i) CCHK(c, hipMalloc(&c->a[i], nv * 16 * sizeof(uint16_t)));
   for (int i = 0; i < 4; ++i) CCHK(c, hipMalloc(&c->z[i], nv * (i < 3 ? 16 : 2) * sizeof(float)));
   for (int i = 0; i < 4; ++i) CCHK(c, hipMalloc(&c->dz[i], nv * 16 * sizeof(uint16_t)));
@@ -632,12 +640,10 @@ hmc_status ensure(cnn_ctx* c, int n) {
   return HMC_OK;
 }
 
-// TRAIN: keeps the pre-activations and the rounded input; out0 / out1: see k_conv
+// TRAIN: keeps the pre-activations; out0 / out1: see k_conv
 template <bool TRAIN>
 hmc_status forward_t(cnn_ctx* c, int n, const float* in3, float* mu, float* logvar) {
-  const long long nv = (long long)n * n * n;
   const dim3 g(conv_bricks(n)), b(256);
-  if (TRAIN) hipLaunchKernelGGL(k_input, dim3(4096), b, 0, c->stream, nv, in3, c->a0);
   hipLaunchKernelGGL((k_conv<4, C_FWD_GELU, TRAIN>), g, b, 0, c->stream, n, in3, c->wp[0],
                      c->p + off_b(0), nullptr, c->z[0], nullptr, c->a[0]);
   for (int l = 1; l < 3; ++l)
@@ -665,30 +671,17 @@ hmc_status gradient(cnn_ctx* c, int n, const float* in3, const float* target, do
   const long long nv = (long long)n * n * n;
   hipLaunchKernelGGL(k_loss, dim3(1024), dim3(256), 0, c->stream, nv, (const float2*)c->z[3], target,
                      (uint4*)c->dz[3], c->lpart);
-  const long long nchunks = nv / 16;
-  const bool lds = n % kBZ == 0;
-  const int nbricks = lds ? (n / kBX) * (n / kBY) * (n / kBZ) : 0;
-  const int cpw = (int)((nchunks + kWaves - 1) / kWaves);
-  const int gblocks = lds ? std::min(nbricks, kWaves / 4) : 0;
-  const int nw = lds ? 4 * gblocks : (int)((nchunks + cpw - 1) / cpw);
-  const int wblocks = (nw + 3) / 4;
+  const int blocks = std::min(wgrad_bricks(n), c->parts);
   for (int l = 3; l >= 0; --l) {
-    const uint16_t* ain = l == 0 ? c->a0 : c->a[l - 1];
     const uint16_t* dz = c->dz[l];
-    if (lds && l == 0)
-      hipLaunchKernelGGL(k_wgrad_lds<4>, dim3(gblocks), dim3(256), 0, c->stream, n, ain, dz,
-                         c->wpart, c->dbpart);
-    else if (lds)
-      hipLaunchKernelGGL(k_wgrad_lds<16>, dim3(gblocks), dim3(256), 0, c->stream, n, ain, dz,
-                         c->wpart, c->dbpart);
-    else if (l == 0)
-      hipLaunchKernelGGL(k_wgrad<4>, dim3(wblocks), dim3(256), 0, c->stream, n, ain, dz, cpw,
-                         c->wpart, c->dbpart);
+    if (l == 0)
+      hipLaunchKernelGGL(k_wgrad<4>, dim3(blocks), dim3(256), 0, c->stream, n, in3, dz, c->wpart,
+                         c->dbpart);
     else
-      hipLaunchKernelGGL(k_wgrad<16>, dim3(wblocks), dim3(256), 0, c->stream, n, ain, dz, cpw,
+      hipLaunchKernelGGL(k_wgrad<16>, dim3(blocks), dim3(256), 0, c->stream, n, c->a[l - 1], dz,
                          c->wpart, c->dbpart);
     hipLaunchKernelGGL(k_wreduce, dim3(kRedBlocks + 1), dim3(1024), 0, c->stream, c->wpart,
-                       c->dbpart, nw, kCin[l], kCout[l], c->g + off_w(l), c->g + off_b(l));
+                       c->dbpart, blocks, kCin[l], kCout[l], c->g + off_w(l), c->g + off_b(l));
     if (l > 0)
       hipLaunchKernelGGL((k_conv<16, C_DGRAD, true>), dim3(conv_bricks(n)), dim3(256), 0, c->stream,
                          n, dz, c->wd[l], nullptr, c->z[l - 1], nullptr, nullptr, c->dz[l - 1]);
@@ -743,6 +736,11 @@ hmc_status cnn_create(const float* params, void* stream, cnn_ctx** out) {
     return HMC_EDEVICE;
   };
   hipError_t e;
+  int dev = 0;
+  if ((e = hipGetDevice(&dev)) != hipSuccess ||
+      (e = hipDeviceGetAttribute(&c->parts, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess)
+    return bail("device attributes", e);
+  c->parts *= 3;
   // g holds the gradient and, past its end, the last layer's bias padded to 16
   if ((e = hipMalloc(&c->p, np * sizeof(float))) != hipSuccess) return bail("hipMalloc", e);
   if ((e = hipMalloc(&c->g, n_grad() * sizeof(float))) != hipSuccess) return bail("hipMalloc", e);
@@ -753,9 +751,9 @@ hmc_status cnn_create(const float* params, void* stream, cnn_ctx** out) {
       return bail("hipMalloc", e);
     if ((e = hipMalloc(&c->wd[l], 27 * 64 * sizeof(bf16x4))) != hipSuccess) return bail("hipMalloc", e);
   }
-  if ((e = hipMalloc(&c->wpart, (size_t)kWaves * 27 * 256 * sizeof(float))) != hipSuccess)
+  if ((e = hipMalloc(&c->wpart, (size_t)c->parts * kTile * sizeof(float))) != hipSuccess)
     return bail("hipMalloc", e);
-  if ((e = hipMalloc(&c->dbpart, (size_t)kWaves * 16 * sizeof(float))) != hipSuccess)
+  if ((e = hipMalloc(&c->dbpart, (size_t)c->parts * 16 * sizeof(float))) != hipSuccess)
     return bail("hipMalloc", e);
   if ((e = hipMalloc(&c->lpart, 1024 * sizeof(double))) != hipSuccess) return bail("hipMalloc", e);
   if ((e = hipHostMalloc((void**)&c->lpart_h, 1024 * sizeof(double), 0)) != hipSuccess)
