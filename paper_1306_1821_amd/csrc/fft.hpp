@@ -35,7 +35,11 @@ __device__ __forceinline__ float2 cmul(float2 a, float2 b) {
   return make_float2(__builtin_fmaf(a.x, b.x, -(a.y * b.y)), __builtin_fmaf(a.x, b.y, a.y * b.x));
 }
 __device__ __forceinline__ float2 cconj(float2 a) { return make_float2(a.x, -a.y); }
-__device__ __forceinline__ float2 cscale(float2 a, float s) { return make_float2(a.x * s, a.y * s); }
+// rounded as written: its products are not contracted into the sums they feed (see cmul)
+__device__ __forceinline__ float2 cscale(float2 a, float s) {
+#pragma clang fp contract(off)
+  return make_float2(a.x * s, a.y * s);
+}
 
 // -------------------------------------------------------------- compile-time trig
 constexpr double kPi = 3.14159265358979323846264338327950288;

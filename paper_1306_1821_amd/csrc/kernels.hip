@@ -609,6 +609,29 @@ __device__ __forceinline__ void bins_flush(B* bins, double* dst, int nb, int str
   __syncthreads();
 }
 
+// One element's kick p_hat -= k (delta_hat / lambda + g_hat) and drift delta_hat += s p_hat / m,
+// and one voxel pair's data force, with the fused multiply-adds written out (see cmul)
+__device__ __forceinline__ float2 kicked(float2 p, float2 x, float2 g, float k, float il) {
+  return make_float2(__builtin_fmaf(-k, __builtin_fmaf(x.x, il, g.x), p.x),
+                     __builtin_fmaf(-k, __builtin_fmaf(x.y, il, g.y), p.y));
+}
+__device__ __forceinline__ float2 drifted(float2 x, float2 p, float s, float im) {
+  return make_float2(__builtin_fmaf(s * p.x, im, x.x), __builtin_fmaf(s * p.y, im, x.y));
+}
+__device__ __forceinline__ float2 data_force(float2 a, float2 x, float2 b) {
+  return make_float2(__builtin_fmaf(a.x, x.x, -b.x), __builtin_fmaf(a.y, x.y, -b.y));
+}
+
+// The float64 energy terms: acc + w |p|^2 c of one mode, and (alpha / 2 x - beta) x of a voxel pair
+__device__ __forceinline__ double mode_energy(double acc, double w, float2 p, double c) {
+  return __builtin_fma(w * ((double)p.x * p.x + (double)p.y * p.y), c, acc);
+}
+__device__ __forceinline__ double voxel_energy(float2 a, float2 x, float2 b) {
+  const double px = __builtin_fma(0.5 * a.x, (double)x.x, -(double)b.x);
+  const double py = __builtin_fma(0.5 * a.y, (double)x.y, -(double)b.y);
+  return __builtin_fma(px, (double)x.x, py * (double)x.y);
+}
+
 // ------------------------------------------------------------------ x pass
 // Thread (t, b) of a block holds elements kx = t + T e (e < E) of mode column
 // col = tile B + b (ky = col / H, kz = col % H).  Idle lanes of the last tile read
@@ -756,28 +779,24 @@ __device__ __forceinline__ void xpass(const ChainDev& d, int lt, const XArgs a, 
           gsti(d.bgk, offs(e), g);
         }
         if (active && me >= 0) {
-          acc0 += wz * ((double)pk.x * pk.x + (double)pk.y * pk.y) * gldd(td + kDInvMass + me);
-          acc1 += wz * ((double)dk.x * dk.x + (double)dk.y * dk.y) * gldd(td + kDInvLam + me);
+          acc0 = mode_energy(acc0, wz, pk, gldd(td + kDInvMass + me));
+          acc1 = mode_energy(acc1, wz, dk, gldd(td + kDInvLam + me));
         }
       } else {
         g = cscale(v[e], norm);
         pk = pkv[e];
       }
       if (me >= 0) {
-        pk.x -= kick * (dk.x * il + g.x);
-        pk.y -= kick * (dk.y * il + g.y);
-        if constexpr (MODE != X_END) {
-          dk.x += drift * pk.x * im;
-          dk.y += drift * pk.y * im;
-        }
+        pk = kicked(pk, dk, g, kick, il);
+        if constexpr (MODE != X_END) dk = drifted(dk, pk, drift, im);
       } else {
         pk = make_float2(0.f, 0.f);
         dk = make_float2(0.f, 0.f);
       }
       if constexpr (MODE == X_END) {
         if (active && me >= 0) {
-          acc0 += wz * ((double)pk.x * pk.x + (double)pk.y * pk.y) * gldd(td + kDInvMass + me);
-          acc1 += wz * ((double)dk.x * dk.x + (double)dk.y * dk.y) * gldd(td + kDInvLam + me);
+          acc0 = mode_energy(acc0, wz, pk, gldd(td + kDInvMass + me));
+          acc1 = mode_energy(acc1, wz, dk, gldd(td + kDInvLam + me));
         }
         if (active) {
           gsti(pkb, offs(e), pk);
@@ -913,6 +932,47 @@ __global__ void __launch_bounds__((xthreads<N, P>())) k_ypass_n(const ChainDev* 
   }
 }
 
+// white noise w_i of a row from Philox (streams 3 momenta, 11 warm start), element = voxel
+// index, in the row's cyclic distribution (voxel pairs t + T e)
+template <int T, int E>
+__device__ __forceinline__ void noise_row(const ChainDev& d, size_t rbase, int t, uint32_t stream,
+                                          float2* v) {
+  if constexpr (T % 2 == 0 && E % 2 == 0) {
+    // One Philox block covers 4 voxels: words 0, 1 go to the voxel pair of lane t
+    // (t even) and words 2, 3 to that of lane t + 1.  For each element pair
+    // (e, e + E/2) the even lane computes the block of e, the odd lane that of
+    // e + E/2, and each hands its partner the two words the partner needs.
+    const bool odd = t & 1;
+#pragma unroll
+    for (int e = 0; e < E / 2; ++e) {
+      const uint64_t vox = rbase + 2 * (uint64_t)(t + T * (odd ? e + E / 2 : e));
+      const hmcrng::U4 w = hmcrng::block(d.seed, d.chain, stream, *d.draw, 0,
+                                         (uint32_t)(vox >> 2));
+      const uint32_t own0 = odd ? w.w[2] : w.w[0], own1 = odd ? w.w[3] : w.w[1];
+      const uint32_t r0 = __shfl_xor(odd ? w.w[0] : w.w[2], 1);
+      const uint32_t r1 = __shfl_xor(odd ? w.w[1] : w.w[3], 1);
+      double z0, z1;
+      hmcrng::box_muller(odd ? r0 : own0, odd ? r1 : own1, &z0, &z1);
+      v[e] = make_float2((float)z0, (float)z1);
+      hmcrng::box_muller(odd ? own0 : r0, odd ? own1 : r1, &z0, &z1);
+      v[e + E / 2] = make_float2((float)z0, (float)z1);
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const uint64_t vox = rbase + 2 * (uint64_t)(t + T * e);
+      const hmcrng::U4 w = hmcrng::block(d.seed, d.chain, stream, *d.draw, 0,
+                                         (uint32_t)(vox >> 2));
+      double z0, z1;
+      if (((vox >> 1) & 1) == 0)
+        hmcrng::box_muller(w.w[0], w.w[1], &z0, &z1);
+      else
+        hmcrng::box_muller(w.w[2], w.w[3], &z0, &z1);
+      v[e] = make_float2((float)z0, (float)z1);
+    }
+  }
+}
+
 // ------------------------------------------------------------------ z pass
 // twM: W_M^i (i < M), twN: W_N^k (k < M), in global memory or staged in LDS
 template <int N, int MODE, int P = 0>
@@ -960,42 +1020,8 @@ __device__ __forceinline__ void zpass_t(const ChainDev& d, int lt, const ZArgs a
 #pragma unroll
     for (int e = 0; e < E; ++e)
       v[e] = gldi(reinterpret_cast<const float2*>(a.src), ro + t + T * e);
-  } else {  // Z_NOISE: white noise w_i from Philox stream 3 (11: warm start), element = voxel index
-    const uint32_t stream = (a.flags & ZF_WARM) ? hmcrng::kWarm : hmcrng::kMomenta;
-    if constexpr (T % 2 == 0 && E % 2 == 0) {
-      // One Philox block covers 4 voxels: words 0, 1 go to the voxel pair of lane t
-      // (t even) and words 2, 3 to that of lane t + 1.  For each element pair
-      // (e, e + E/2) the even lane computes the block of e, the odd lane that of
-      // e + E/2, and each hands its partner the two words the partner needs.
-      const bool odd = t & 1;
-#pragma unroll
-      for (int e = 0; e < E / 2; ++e) {
-        const uint64_t vox = rbase + 2 * (uint64_t)(t + T * (odd ? e + E / 2 : e));
-        const hmcrng::U4 w = hmcrng::block(d.seed, d.chain, stream, *d.draw, 0,
-                                           (uint32_t)(vox >> 2));
-        const uint32_t own0 = odd ? w.w[2] : w.w[0], own1 = odd ? w.w[3] : w.w[1];
-        const uint32_t r0 = __shfl_xor(odd ? w.w[0] : w.w[2], 1);
-        const uint32_t r1 = __shfl_xor(odd ? w.w[1] : w.w[3], 1);
-        double z0, z1;
-        hmcrng::box_muller(odd ? r0 : own0, odd ? r1 : own1, &z0, &z1);
-        v[e] = make_float2((float)z0, (float)z1);
-        hmcrng::box_muller(odd ? own0 : r0, odd ? own1 : r1, &z0, &z1);
-        v[e + E / 2] = make_float2((float)z0, (float)z1);
-      }
-    } else {
-#pragma unroll
-      for (int e = 0; e < E; ++e) {
-        const uint64_t vox = rbase + 2 * (uint64_t)(t + T * e);
-        const hmcrng::U4 w = hmcrng::block(d.seed, d.chain, stream, *d.draw, 0,
-                                           (uint32_t)(vox >> 2));
-        double z0, z1;
-        if (((vox >> 1) & 1) == 0)
-          hmcrng::box_muller(w.w[0], w.w[1], &z0, &z1);
-        else
-          hmcrng::box_muller(w.w[2], w.w[3], &z0, &z1);
-        v[e] = make_float2((float)z0, (float)z1);
-      }
-    }
+  } else {
+    noise_row<T, E>(d, rbase, t, (a.flags & ZF_WARM) ? hmcrng::kWarm : hmcrng::kMomenta, v);
   }
 
   if constexpr (MODE == Z_GRAD || MODE == Z_C2R) {
@@ -1015,8 +1041,8 @@ __device__ __forceinline__ void zpass_t(const ChainDev& d, int lt, const ZArgs a
           bq = ld_si(reinterpret_cast<const float2*>(d.beta), ro + n);
         }
         if (active && (a.flags & ZF_DATA))
-          dat += (0.5 * ae.x * x.x - bq.x) * (double)x.x + (0.5 * ae.y * x.y - bq.y) * (double)x.y;
-        v[e] = make_float2(ae.x * x.x - bq.x, ae.y * x.y - bq.y);
+          dat += voxel_energy(ae, x, bq);
+        v[e] = data_force(ae, x, bq);
       }
     }
   }
@@ -1286,10 +1312,8 @@ __device__ __forceinline__ void yzpass(const ChainDev& d, int x, const ZArgs a, 
     for (int e = 0; e < EZ; ++e) {
       const float2 xv = w[e];
       if (FULL && drout) gsti(reinterpret_cast<float2*>(drout) + rq + TZ * e, ro, xv);  // trajectory ends
-      if (data)
-        dat += (0.5 * al[e].x * xv.x - be[e].x) * (double)xv.x +
-               (0.5 * al[e].y * xv.y - be[e].y) * (double)xv.y;
-      w[e] = make_float2(al[e].x * xv.x - be[e].x, al[e].y * xv.y - be[e].y);
+      if (data) dat += voxel_energy(al[e], xv, be[e]);
+      w[e] = data_force(al[e], xv, be[e]);
     }
     if constexpr (q + 1 < NCH) load_ab(q + 1);
     zfft<M, TZ, +1, typename C::RLZ>(w, Lr, tz, true, twM);
@@ -1464,9 +1488,7 @@ __device__ __forceinline__ void zpass_l(const ChainDev& d, int lt, const ZArgs a
       const float g0 = fp.x + al[e].x * x.x - be[e].x, g1 = fp.y + al[e].y * x.y - be[e].y;
       if (active) {
         sum += (double)g0 + (double)g1;
-        if (a.flags & ZF_DATA)
-          dat += (0.5 * al[e].x * x.x - be[e].x) * (double)x.x +
-                 (0.5 * al[e].y * x.y - be[e].y) * (double)x.y;
+        if (a.flags & ZF_DATA) dat += voxel_energy(al[e], x, be[e]);
       }
       v[e] = make_float2(s[e].x * g0, s[e].y * g1);
     }
@@ -1544,8 +1566,8 @@ __device__ __forceinline__ void xpass_l(const ChainDev& d, int lt, const XArgs a
         gsti(d.bgk, offs(e), w[e]);
         xst(d.pk, offs(e), pk);
         if (me >= 0) {
-          acc0 += wz * ((double)pk.x * pk.x + (double)pk.y * pk.y) * gldd(td + kDInvMass + me);
-          acc1 += wz * ((double)dk.x * dk.x + (double)dk.y * dk.y) * gldd(td + kDInvLam + me);
+          acc0 = mode_energy(acc0, wz, pk, gldd(td + kDInvMass + me));
+          acc1 = mode_energy(acc1, wz, dk, gldd(td + kDInvLam + me));
         }
       }
       v[e] = cscale(dk, norm);
@@ -1570,8 +1592,8 @@ __device__ __forceinline__ void xpass_l(const ChainDev& d, int lt, const XArgs a
       if constexpr (MODE == L_KICK_LAST) {
         if (active && me >= 0) {
           const float2 dk = xld(d.dk, offs(e));
-          acc0 += wz * ((double)pk.x * pk.x + (double)pk.y * pk.y) * gldd(td + kDInvMass + me);
-          acc1 += wz * ((double)dk.x * dk.x + (double)dk.y * dk.y) * gldd(td + kDInvLam + me);
+          acc0 = mode_energy(acc0, wz, pk, gldd(td + kDInvMass + me));
+          acc1 = mode_energy(acc1, wz, dk, gldd(td + kDInvLam + me));
         }
       } else {
         v[e] = me >= 0 ? cscale(pk, norm * tf[kTInvMass + me]) : z2;
@@ -2376,14 +2398,12 @@ __global__ void k_tables(const ChainDev* __restrict__ ch) {
 }
 
 // Metropolis test of eq. acceptance_rule: accept iff ln u < -dH (u: Philox stream 4)
-__global__ void k_accept(const ChainDev* __restrict__ ch) {
-  const ChainDev& d = ch[blockIdx.x];
-  if (threadIdx.x != 0) return;
-  const uint32_t traj = *d.draw;
-  const double H0 = d.P[kK0] + d.P[kPi0] + d.P[kDcur];
-  const double H1 = d.P[kK1] + d.P[kPi1] + d.P[kD1];
+__device__ __forceinline__ bool accept_chain(const ChainDev& d, double K0, double Pi0, double K1,
+                                             double Pi1, double D1) {
+  const double H0 = K0 + Pi0 + d.P[kDcur];
+  const double H1 = K1 + Pi1 + D1;
   const double dH = H1 - H0;
-  const hmcrng::U4 w = hmcrng::block(d.seed, d.chain, hmcrng::kAccept, traj, 0, 0);
+  const hmcrng::U4 w = hmcrng::block(d.seed, d.chain, hmcrng::kAccept, *d.draw, 0, 0);
   const double lu = log(hmcrng::uniform(w.w[0]));
   const bool finite = isfinite(dH);
   const bool acc = finite && lu < -dH;
@@ -2391,7 +2411,13 @@ __global__ void k_accept(const ChainDev* __restrict__ ch) {
   d.P[kLogU] = lu;
   d.P[kAcc] = acc ? 1.0 : 0.0;
   d.P[kStatus] = finite ? 0.0 : 1.0;
-  if (acc) d.P[kDcur] = d.P[kD1];
+  if (acc) d.P[kDcur] = D1;
+  return acc;
+}
+__global__ void k_accept(const ChainDev* __restrict__ ch) {
+  const ChainDev& d = ch[blockIdx.x];
+  if (threadIdx.x != 0) return;
+  accept_chain(d, d.P[kK0], d.P[kPi0], d.P[kK1], d.P[kPi1], d.P[kD1]);
 }
 
 // P_m | delta: lambda_m = sigma_m / x_m, x_m ~ chi^2(n_m + 2 alpha - 2) = 2 Gamma(.)
@@ -2461,6 +2487,22 @@ __device__ int rj_reflect(double* th, double* rho, double lo, double hi) {
   return hits;
 }
 
+// Metropolis test of the joint move (u: Philox stream 9)
+__device__ __forceinline__ bool rj_accept(const ChainDev& d, double k1, double st, double hits,
+                                          double D1) {
+  d.P[kRjHits] = hits;
+  const double H0 = d.P[kRjK0] + d.P[kRjU0];
+  const double H1 = k1 + D1 + (d.alpha_prior - 1.0) * st;
+  const double dH = H1 - H0;
+  const hmcrng::U4 w = hmcrng::block(d.seed, d.chain, hmcrng::kRjAccept, *d.draw, 0, 0);
+  const double lu = log(hmcrng::uniform(w.w[0]));
+  const bool acc = isfinite(dH) && lu < -dH;
+  d.P[kRjDH] = dH;
+  d.P[kRjAcc] = acc ? 1.0 : 0.0;
+  if (acc) d.P[kDcur] = D1;
+  return acc;
+}
+
 __global__ void __launch_bounds__(kThreads) k_rj(const ChainDev* __restrict__ ch, int phase) {
   __shared__ double red[4];
   const ChainDev& d = ch[blockIdx.x];
@@ -2523,22 +2565,423 @@ __global__ void __launch_bounds__(kThreads) k_rj(const ChainDev* __restrict__ ch
     const double st = block_sum(on ? th : 0.0, red);
     const double hits = block_sum(on ? d.P[kWall + m] : 0.0, red);
     __shared__ int acc_s;
-    if (m == 0) {
-      d.P[kRjHits] = hits;
-      const double H0 = d.P[kRjK0] + d.P[kRjU0];
-      const double H1 = k1 + d.P[kD1] + am1 * st;
-      const double dH = H1 - H0;
-      const hmcrng::U4 w = hmcrng::block(d.seed, d.chain, hmcrng::kRjAccept, sweep, 0, 0);
-      const double lu = log(hmcrng::uniform(w.w[0]));
-      const bool acc = isfinite(dH) && lu < -dH;
-      d.P[kRjDH] = dH;
-      d.P[kRjAcc] = acc ? 1.0 : 0.0;
-      if (acc) d.P[kDcur] = d.P[kD1];
-      acc_s = acc;
-    }
+    if (m == 0) acc_s = rj_accept(d, k1, st, hits, d.P[kD1]);
     __syncthreads();
     if (on && acc_s) d.P[kLam + m] = exp(th);
   }
+}
+
+// ------------------------------------------------------------------ small grids
+// 8^3 and 16^3: a whole trajectory, or all steps of a joint move, of one chain in one
+// workgroup.  Launched pass by pass these grids have one to three tiles per launch and a
+// step is four to six launches of 2 to 4 us, all latency; here the intermediate grid stays
+// in LDS (2.6 or 18.4 KB) and the state (delta_hat, p_hat, alpha, beta) in registers, so
+// a step is a chain of LDS exchanges: an 8^3 trajectory of 20 steps takes 265 us launched
+// and 70 us here (47 us of kernel), a 16^3 sweep with the joint move 1031 and 373 us (91 us
+// the trajectory, 115 us the move).  From 32^3 on the grid no longer fits with its
+// exchange buffers and a single compute unit's LDS is slower than the passes on many.
+//
+// The workgroup is one sub-block of kThreads threads per x / y tile of the passes; a
+// sub-block does for its tile exactly what the passes' workgroups do (thread and pencil
+// shapes, radices, products, partial sums per tile and their order), so the results are
+// bit for bit those of the separate passes, which run when pass timing is on.  Backups
+// are not needed: the caller's arrays keep the start state until the Metropolis test.
+constexpr bool small_grid(int n) { return n == 8 || n == 16; }
+template <int N> struct SG {
+  using X = XC<N>;
+  using Z = ZC<N>;
+  static constexpr int M = N / 2, H = M + 1, NH = N * N * H;
+  static constexpr int TX = X::T, BX = X::B, EX = N / TX, ES = BX + 1;
+  static constexpr int TZ = Z::T, BZ = Z::B, EZ = M / TZ;
+  static constexpr int NTX = (N * H + BX - 1) / BX, NTZ = (N * N + BZ - 1) / BZ;  // tiles
+  static constexpr int S = NTX > NTZ ? NTX : NTZ, P = S * kThreads;
+  static constexpr int EXL = N * ES > BZ * zrs<N>() ? N * ES : BZ * zrs<N>();
+  static_assert(S <= 4 && TX * BX == kThreads && TZ * BZ == kThreads, "small-grid tiles");
+};
+template <int N> struct SmallLds {
+  float2 T[SG<N>::NH];
+  float2 ex[SG<N>::S][SG<N>::EXL];  // transform exchanges
+  float2 twm[N / 2], twn[N];        // W_M^i, W_N^i
+  float tf[kTSize];                 // the chain's float shell tables
+  double red[SG<N>::S][4];
+  double part[5][4];                // per-tile sums: K0, Pi0, K1, Pi1, D1
+  int acc;
+};
+template <int N> struct SmallBins {  // joint move: shell products per sub-block, then per tile
+  bin_t bins[SG<N>::S][kBinSlots];
+  double tile[SG<N>::S][kMaxBins];
+};
+
+template <int N> struct Small {
+  using G = SG<N>;
+  static constexpr int EX = G::EX, EZ = G::EZ, H = G::H, M = G::M;
+  const ChainDev& d;
+  SmallLds<N>& s;
+  int sub, tid;           // sub-block and thread in it
+  int b, t;               // x / y pencil and its thread
+  int zt, row;            // z row and its thread
+  bool xon, zon;
+  uint32_t xo, yo;        // first element of the x and y pencils in T
+  float norm;
+  double wz;
+  int m[EX];              // shells of the x pencil's elements
+  float2 al[EZ], be[EZ];  // alpha, beta of the z row
+
+  __device__ __forceinline__ Small(const ChainDev& d_, SmallLds<N>& s_) : d(d_), s(s_) {
+    sub = threadIdx.x / kThreads;
+    tid = threadIdx.x % kThreads;
+    b = tid % G::BX;
+    t = tid / G::BX;
+    const int col = sub * G::BX + b;
+    xon = sub < G::NTX && col < N * H;
+    const int c = xon ? col : 0;
+    xo = c;
+    yo = (c / H) * (N * H) + c % H;
+    zt = tid % G::TZ;
+    row = sub * G::BZ + tid / G::TZ;
+    zon = sub < G::NTZ && row < N * N;
+    if (!zon) row = 0;
+    norm = d.norm;
+    const int kz = c % H, fy = sfreq(c / H, N);
+    wz = (kz == 0 || kz == M) ? 1.0 : 2.0;
+    constexpr uint32_t qmax = 3u * M * M;
+#pragma unroll
+    for (int e = 0; e < EX; ++e) {
+      const int fx = sfreq(t + G::TX * e, N);
+      m[e] = shell_fast((uint32_t)(fy * fy + kz * kz + fx * fx), qmax, 1.f / (float)qmax, (uint32_t)d.nb);
+    }
+#pragma unroll
+    for (int e = 0; e < EZ; ++e) {
+      al[e] = gldi(reinterpret_cast<const float2*>(d.alpha), vox(e));
+      be[e] = gldi(reinterpret_cast<const float2*>(d.beta), vox(e));
+    }
+  }
+  __device__ __forceinline__ void stage_tables(const float2* tw) {
+    for (int i = threadIdx.x; i < N; i += G::P) {
+      s.twn[i] = tw[tw_offset(N) + i];
+      if (i < M) s.twm[i] = tw[tw_offset(M) + i];
+    }
+    for (int i = threadIdx.x; i < kTSize; i += G::P) s.tf[i] = (i % kMaxBins) < d.nb ? gldf(d.tf + i) : 0.f;
+  }
+  __device__ __forceinline__ uint32_t kidx(int e) const { return xo + (uint32_t)((t + G::TX * e) * N * H); }
+  __device__ __forceinline__ uint32_t vox(int e) const { return (uint32_t)(row * M + zt + G::TZ * e); }
+  // the sub-block's block_sum
+  __device__ __forceinline__ double sum(double v) {
+    v = wave_sum(v);
+    __syncthreads();
+    if ((tid & 63) == 0) s.red[sub][tid >> 6] = v;
+    __syncthreads();
+    return s.red[sub][0] + s.red[sub][1] + s.red[sub][2] + s.red[sub][3];
+  }
+  // sum of up to four tiles' partials in the order of the column sums' butterfly
+  __device__ __forceinline__ static double tiles(const double* p, int n) {
+    return (p[0] + (n > 2 ? p[2] : 0.0)) + ((n > 1 ? p[1] : 0.0) + (n > 3 ? p[3] : 0.0));
+  }
+  __device__ __forceinline__ void xload(float2* v) {
+#pragma unroll
+    for (int e = 0; e < EX; ++e) v[e] = s.T[kidx(e)];
+  }
+  __device__ __forceinline__ void xstore(const float2* v) {
+    if (xon) {
+#pragma unroll
+      for (int e = 0; e < EX; ++e) s.T[kidx(e)] = v[e];
+    }
+    __syncthreads();
+  }
+  template <int DIR> __device__ __forceinline__ void xfft(float2* v) {
+    fft<N, G::TX, DIR>(v, s.ex[sub] + b, G::ES, t, xon, s.twn, typename XC<N>::RL{});
+  }
+  template <int DIR> __device__ __forceinline__ void ypass() {
+    float2 v[EX];
+#pragma unroll
+    for (int e = 0; e < EX; ++e) v[e] = s.T[yo + (t + G::TX * e) * H];
+    xfft<DIR>(v);
+    if (xon) {
+#pragma unroll
+      for (int e = 0; e < EX; ++e) s.T[yo + (t + G::TX * e) * H] = v[e];
+    }
+    __syncthreads();
+  }
+  __device__ __forceinline__ void zforward(float2* v) {
+    float2* const L = s.ex[sub] + tid / G::TZ * zrs<N>();
+    zfft<M, G::TZ, +1, typename ZC<N>::RL>(v, L, zt, zon, s.twm);
+    float2* const T = s.T + row * H;
+    r2c_post<N, G::TZ, EZ>(v, L, zt, zon, s.twn, [&](int k, float2 x) { T[k] = x; });
+    __syncthreads();
+  }
+  // inverse y, C2R, data force, R2C, forward y; x: the real field, dat: its data energy
+  template <bool DATA> __device__ __forceinline__ void yz(float2* x, double* dat) {
+    ypass<-1>();
+    float2* const L = s.ex[sub] + tid / G::TZ * zrs<N>();
+    const float2* const T = s.T + row * H;
+    float2 xr[EZ + 1], v[EZ];
+#pragma unroll
+    for (int e = 0; e < EZ; ++e) xr[e] = T[zt + G::TZ * e];
+    xr[EZ] = T[M];
+    c2r_pre<N, G::TZ, EZ>(xr, v, L, zt, s.twn);
+    zfft<M, G::TZ, -1, typename ZC<N>::RL>(v, L, zt, zon, s.twm);
+    double acc = 0.0;
+#pragma unroll
+    for (int e = 0; e < EZ; ++e) {
+      const float2 xv = v[e], ae = al[e], bq = be[e];
+      if (DATA) {
+        x[e] = xv;
+        if (zon) acc += voxel_energy(ae, xv, bq);
+      }
+      v[e] = data_force(ae, xv, bq);
+    }
+    if (DATA) *dat = acc;
+    zforward(v);
+    ypass<+1>();
+  }
+  __device__ __forceinline__ void store_real(const float2* x) {
+    if (zon) {
+#pragma unroll
+      for (int e = 0; e < EZ; ++e) gsti(reinterpret_cast<float2*>(d.dr), vox(e), x[e]);
+    }
+  }
+};
+
+template <int N>
+__global__ void __launch_bounds__(SG<N>::P) k_small_trajectory(const ChainDev* __restrict__ ch,
+                                                               int steps, const float2* __restrict__ tw) {
+  using G = SG<N>;
+  constexpr int EX = G::EX, EZ = G::EZ;
+  __shared__ SmallLds<N> s;
+  const ChainDev& d = ch[blockIdx.x];
+  Small<N> g(d, s);
+  g.stage_tables(tw);
+  float2 dk[EX], pk[EX], gr[EX], v[EX], x[EZ];
+#pragma unroll
+  for (int e = 0; e < EX; ++e) {
+    dk[e] = gldi(d.dk, g.kidx(e));
+    gr[e] = gldi(d.gk, g.kidx(e));
+  }
+  const float eps = d.eps, norm = g.norm;
+  float2 w[EZ];
+  noise_row<G::TZ, EZ>(d, (size_t)g.row * N, g.zt, hmcrng::kMomenta, w);
+  __syncthreads();  // tables
+  g.zforward(w);
+  g.template ypass<+1>();
+  g.xload(v);
+  g.template xfft<+1>(v);
+  // momentum p_hat = sqrt(m_k) F w, then kick, drift and inverse x transform per step
+  double k0 = 0.0, p0 = 0.0;
+#pragma unroll
+  for (int e = 0; e < EX; ++e) {
+    const int me = g.m[e];
+    const float sq = me >= 0 ? s.tf[kTSqrtMass + me] : 0.f;
+    pk[e] = cscale(v[e], norm * sq);
+    if (g.xon && me >= 0) {
+      k0 = mode_energy(k0, g.wz, pk[e], gldd(d.td + kDInvMass + me));
+      p0 = mode_energy(p0, g.wz, dk[e], gldd(d.td + kDInvLam + me));
+    }
+  }
+  auto kick = [&](float ek, float ed, bool last) {
+#pragma unroll
+    for (int e = 0; e < EX; ++e) {
+      const int me = g.m[e];
+      const float il = me >= 0 ? s.tf[kTInvLam + me] : 0.f;
+      const float im = me >= 0 ? s.tf[kTInvMass + me] : 0.f;
+      if (me >= 0) {
+        pk[e] = kicked(pk[e], dk[e], gr[e], ek, il);
+        if (!last) dk[e] = drifted(dk[e], pk[e], ed, im);
+      } else {
+        pk[e] = make_float2(0.f, 0.f);
+        dk[e] = make_float2(0.f, 0.f);
+      }
+      if (!last) v[e] = cscale(dk[e], norm);
+    }
+  };
+  const double K0 = g.sum(0.5 * k0), Pi0 = g.sum(0.5 * p0);
+  if (g.tid == 0 && g.sub < G::NTX) {
+    s.part[0][g.sub] = K0;
+    s.part[1][g.sub] = Pi0;
+  }
+  kick(0.5f * eps, 1.f * eps, false);
+  g.template xfft<-1>(v);
+  g.xstore(v);
+  for (int i = 1; i < steps; ++i) {
+    g.template yz<false>(nullptr, nullptr);
+    g.xload(v);
+    g.template xfft<+1>(v);
+#pragma unroll
+    for (int e = 0; e < EX; ++e) gr[e] = cscale(v[e], norm);
+    kick(1.f * eps, 1.f * eps, false);
+    g.template xfft<-1>(v);
+    g.xstore(v);
+  }
+  double dat;
+  g.template yz<true>(x, &dat);
+  g.xload(v);
+  g.template xfft<+1>(v);
+#pragma unroll
+  for (int e = 0; e < EX; ++e) gr[e] = cscale(v[e], norm);
+  kick(0.5f * eps, 0.f * eps, true);
+  double k1 = 0.0, p1 = 0.0;
+#pragma unroll
+  for (int e = 0; e < EX; ++e) {
+    const int me = g.m[e];
+    if (g.xon && me >= 0) {
+      k1 = mode_energy(k1, g.wz, pk[e], gldd(d.td + kDInvMass + me));
+      p1 = mode_energy(p1, g.wz, dk[e], gldd(d.td + kDInvLam + me));
+    }
+  }
+  const double K1 = g.sum(0.5 * k1), Pi1 = g.sum(0.5 * p1), D1 = g.sum(dat);
+  if (g.tid == 0) {
+    if (g.sub < G::NTX) {
+      s.part[2][g.sub] = K1;
+      s.part[3][g.sub] = Pi1;
+    }
+    if (g.sub < G::NTZ) s.part[4][g.sub] = D1;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double e[5];
+    for (int i = 0; i < 5; ++i) e[i] = Small<N>::tiles(s.part[i], i < 4 ? G::NTX : G::NTZ);
+    d.P[kK0] = e[0];
+    d.P[kPi0] = e[1];
+    d.P[kK1] = e[2];
+    d.P[kPi1] = e[3];
+    d.P[kD1] = e[4];
+    s.acc = accept_chain(d, e[0], e[1], e[2], e[3], e[4]);
+  }
+  __syncthreads();
+  const bool acc = s.acc;
+  if (g.xon) {
+#pragma unroll
+    for (int e = 0; e < EX; ++e) {
+      gsti(d.pk, g.kidx(e), pk[e]);
+      if (acc) {
+        gsti(d.dk, g.kidx(e), dk[e]);
+        gsti(d.gk, g.kidx(e), g.m[e] < 0 ? make_float2(0.f, 0.f) : gr[e]);
+      }
+    }
+  }
+  if (acc) g.store_real(x);
+}
+
+// the joint move after RJ_BEGIN: every gradient evaluation, step, the Metropolis test and
+// the commit
+template <int N>
+__global__ void __launch_bounds__(SG<N>::P) k_small_joint(const ChainDev* __restrict__ ch, int steps,
+                                                          const float2* __restrict__ tw) {
+  using G = SG<N>;
+  constexpr int EX = G::EX, EZ = G::EZ;
+  __shared__ SmallLds<N> s;
+  __shared__ SmallBins<N> sb;
+  const ChainDev& d = ch[blockIdx.x];
+  Small<N> g(d, s);
+  g.stage_tables(tw);
+  float2 dk[EX], v[EX], x[EZ];
+#pragma unroll
+  for (int e = 0; e < EX; ++e) dk[e] = gldi(d.dk, g.kidx(e));
+  const int m = threadIdx.x;
+  const bool on = m < d.nb;
+  const float norm = g.norm;
+  const double eps = d.eps;
+  double th = 0.0, rho = 0.0, ms = 1.0, th0 = 0.0, lo = 0.0, hi = 0.0, wall = 0.0;
+  if (on) {
+    th = d.P[kTheta + m];
+    rho = d.P[kRho + m];
+    ms = d.P[kMth + m];
+    th0 = d.P[kTheta0 + m];
+    lo = d.P[kLo + m];
+    hi = d.P[kHi + m];
+    wall = d.P[kWall + m];
+  }
+  bin_t* const bins = sb.bins[g.sub];
+  double dat = 0.0;
+  for (int i = 0; i < steps; ++i) {
+    const bool last = i == steps - 1;
+    for (int j = g.tid; j < kBinSlots; j += kThreads) bins[j] = (bin_t)0;
+    __syncthreads();  // the tables / the step's scale factors
+#pragma unroll
+    for (int e = 0; e < EX; ++e) {
+      const int me = g.m[e];
+      float sc = norm;
+      if (me >= 0) sc *= s.tf[kTScale + me];
+      v[e] = me < 0 ? make_float2(0.f, 0.f) : cscale(dk[e], sc);
+    }
+    g.template xfft<-1>(v);
+    g.xstore(v);
+    if (last)
+      g.template yz<true>(x, &dat);
+    else
+      g.template yz<false>(nullptr, nullptr);
+    g.xload(v);
+    g.template xfft<+1>(v);
+#pragma unroll
+    for (int e = 0; e < EX; ++e) {
+      const int me = g.m[e];
+      v[e] = me < 0 ? make_float2(0.f, 0.f) : cscale(v[e], norm);
+      if (g.xon && me >= 0) {
+        const float sc = s.tf[kTScale + me];
+        const double val = g.wz * ((double)(sc * dk[e].x) * v[e].x + (double)(sc * dk[e].y) * v[e].y);
+        atomicAdd(&bins[((g.tid >> 6) * kBinCopies + bin_copy<G::BX>()) * kBinStride + me], (bin_t)val);
+      }
+    }
+    __syncthreads();
+    if (g.tid < d.nb) {
+      double sm = 0.0;
+#pragma unroll
+      for (int j = 0; j < 4 * kBinCopies; ++j) sm += (double)bins[j * kBinStride + g.tid];
+      sb.tile[g.sub][g.tid] = sm;
+    }
+    __syncthreads();
+    if (on) {
+      double p[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) p[j] = j < G::NTX ? sb.tile[j < G::NTX ? j : 0][m] : 0.0;
+      const double dU = 0.5 * Small<N>::tiles(p, G::NTX) + (d.alpha_prior - 1.0);
+      if (!last) {
+        rho -= eps * dU;
+        th += eps * rho / ms;
+        wall += (double)rj_reflect(&th, &rho, lo, hi);
+        s.tf[kTScale + m] = (float)exp(0.5 * (th - th0));
+      } else {
+        rho = rho - 0.5 * eps * dU;
+      }
+    }
+  }
+  const double k1 = g.sum(on ? 0.5 * rho * rho / ms : 0.0);
+  const double st = g.sum(on ? th : 0.0);
+  const double hits = g.sum(on ? wall : 0.0);
+  const double D1 = g.sum(dat);
+  if (g.tid == 0 && g.sub < G::NTZ) s.part[4][g.sub] = D1;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const double e = Small<N>::tiles(s.part[4], G::NTZ);
+    d.P[kD1] = e;
+    s.acc = rj_accept(d, k1, st, hits, e);
+  }
+  __syncthreads();
+  if (!s.acc) return;
+  if (on) d.P[kLam + m] = exp(th);
+  if (g.xon) {
+#pragma unroll
+    for (int e = 0; e < EX; ++e) {
+      const float sc = g.m[e] >= 0 ? s.tf[kTScale + g.m[e]] : 0.f;
+      gsti(d.gk, g.kidx(e), v[e]);
+      gsti(d.dk, g.kidx(e), make_float2(dk[e].x * sc, dk[e].y * sc));
+    }
+  }
+  g.store_real(x);
+}
+
+bool small_grid_supported(int n) { return small_grid(n); }
+void launch_small_trajectory(const ChainDev* ch, int nch, int steps, const float2* tw, hipStream_t s,
+                             int n) {
+  if (n == 8)
+    hipLaunchKernelGGL(k_small_trajectory<8>, dim3(nch), dim3(SG<8>::P), 0, s, ch, steps, tw);
+  else if (n == 16)
+    hipLaunchKernelGGL(k_small_trajectory<16>, dim3(nch), dim3(SG<16>::P), 0, s, ch, steps, tw);
+}
+void launch_small_joint(const ChainDev* ch, int nch, int steps, const float2* tw, hipStream_t s, int n) {
+  if (n == 8)
+    hipLaunchKernelGGL(k_small_joint<8>, dim3(nch), dim3(SG<8>::P), 0, s, ch, steps, tw);
+  else if (n == 16)
+    hipLaunchKernelGGL(k_small_joint<16>, dim3(nch), dim3(SG<16>::P), 0, s, ch, steps, tw);
 }
 
 // ------------------------------------------------------------------ launch wrappers

@@ -69,6 +69,13 @@ void launch_mass_prep(int phase, const ChainDev* ch, int total_r, const float* l
 // for single-size launches of the grid sizes it supports
 bool plane_pass_supported(int n);
 void launch_yzpass(const ChainDev* ch, int nch, ZArgs a, const float2* tw, hipStream_t s, int n);
+// grids whose trajectories and joint moves run in one workgroup per chain (single-size
+// contexts); launch_small_joint follows launch_rj(RJ_BEGIN)
+bool small_grid_supported(int n);
+void launch_small_trajectory(const ChainDev* ch, int nch, int steps, const float2* tw, hipStream_t s,
+                             int n);
+void launch_small_joint(const ChainDev* ch, int nch, int steps, const float2* tw, hipStream_t s,
+                        int n);
 void launch_zpass(int mode, const ChainDev* ch, int nch, int total, int lds, ZArgs a,
                   const float2* tw, int grid_cap, hipStream_t s, int uniform_n, int plan = 0);
 void launch_export(const ChainDev* ch, int nch, int sweep, double* rec, int32_t* acc,

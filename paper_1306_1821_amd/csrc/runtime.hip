@@ -703,10 +703,20 @@ static hmc_status run_trajectory_learned(hmc_ctx* c) {
   return refresh_gradient(c, false);
 }
 
+// contexts of 8^3 or 16^3 chains run a trajectory or joint move in one workgroup per chain,
+// unless the caller times the passes
+static bool one_workgroup(const hmc_ctx* c) {
+  return small_grid_supported(c->uniform_n) && !c->timing;
+}
+
 static hmc_status run_trajectory(hmc_ctx* c) {
   if (c->learned) return run_trajectory_learned(c);
   Seq q = seq_all(c);
   const int nch = (int)c->ch.size();
+  if (one_workgroup(c)) {
+    launch_small_trajectory(c->d_all, nch, c->cur_steps, c->tw, c->stream, c->uniform_n);
+    return check_launch(c);
+  }
   q.z(Z_NOISE, 0);
   q.y(+1);
   q.x(X_START, 0.5f, 1.f, 0);
@@ -814,7 +824,9 @@ static hmc_status run_sweep(hmc_ctx* c) {
     // k-space pass over the stored arrays gives it.
     launch_shell_dot(c->d_all, nch, c->total[kTileK], c->stream);
     launch_rj(RJ_BEGIN, c->d_all, nch, c->max_nb, c->stream, kTileK);
-    for (int i = 0; i < c->cur_steps; ++i) {
+    if (one_workgroup(c))
+      launch_small_joint(c->d_all, nch, c->cur_steps, c->tw, c->stream, c->uniform_n);
+    for (int i = 0; !one_workgroup(c) && i < c->cur_steps; ++i) {
       const bool last = i == c->cur_steps - 1;
       q.gradient(last ? (ZF_WRITE_DRN | ZF_DATA) : 0,
                  XF_SCALE | XF_DOT | (last ? XF_OUT_ALT : XF_NOSTORE));
@@ -825,7 +837,8 @@ static hmc_status run_sweep(hmc_ctx* c) {
         launch_rj(RJ_END, c->d_all, nch, c->max_nb, c->stream);
       }
     }
-    launch_commit(C_RJ, c->d_all, nch, c->total[kTileK], c->total[kTileR], c->stream);
+    if (!one_workgroup(c))
+      launch_commit(C_RJ, c->d_all, nch, c->total[kTileK], c->total[kTileR], c->stream);
     launch_tables(c->d_all, nch, c->stream);
   }
   // Nbar | delta, b and b | delta, Nbar
