@@ -33,9 +33,6 @@
 #ifndef HMC_DOT_F32
 #define HMC_DOT_F32 0
 #endif
-#ifndef HMC_LDS_TAB
-#define HMC_LDS_TAB 1
-#endif
 #ifndef HMC_SHELL_LUT
 #define HMC_SHELL_LUT 0
 #endif
@@ -269,14 +266,18 @@ template <> struct ZPlan<256, 1> { using RL = Radices<4, 4, 8>; };
 template <> struct ZPlan<256, 2> { using RL = Radices<2, 8, 8>; };
 
 template <int N> constexpr int xlds() { return N * (XC<N>::B + 1) * 8; }
-// z-pass LDS row stride in float2: at least M + 2; for M >= 64 rounded up to
-// 16 mod 32 so that the two rows a half-wave reads fall on disjoint LDS banks
+// z-pass LDS row stride in float2: at least M + 2; for M >= 32 the next value that is T mod
+// 32, so that the 64 / T rows a wave reads at once (T float2 each) fall on disjoint banks
+// (with 16 mod 32 for every T, 8-lane rows met two to a bank: plane pass at 192^3, two
+// chains, 87.6 us instead of 83.5; 128^3, four chains, 32.5 instead of 31.5)
 template <int N> constexpr int zrs() {
-  constexpr int M = N / 2;
-  if constexpr (M < 64 || !HMC_ZPAD) {
+  constexpr int M = N / 2, T = ZC<N>::T;
+  if constexpr (M < 32 || !HMC_ZPAD) {
     return M + 2;
   } else {
-    return ((M + 2 + 15) / 32) * 32 + 16;
+    int r = M + 2;
+    while (r % 32 != T || (M - 1) + (M - 1) / 16 >= r) ++r;
+    return r;
   }
 }
 template <int N> constexpr int zlds() { return ZC<N>::B * zrs<N>() * 8; }
@@ -457,6 +458,12 @@ __device__ __forceinline__ int find_chain(const ChainDev* ch, int nch, int tile,
   int c = 0;
   while (c + 1 < nch && tile >= ch[c + 1].tb[cls]) ++c;
   return c;
+}
+
+// the same in a single-size launch: every chain has total / nch tiles (find_chain walks the
+// descriptors one dependent load after another)
+__device__ __forceinline__ int chain_of(int nch, int total, int tile) {
+  return nch == 1 ? 0 : tile / (total / nch);
 }
 
 __device__ __forceinline__ int sfreq(int k, int n) { return k <= n / 2 ? k : k - n; }
@@ -664,15 +671,6 @@ __device__ __forceinline__ void xpass(const ChainDev& d, int lt, const XArgs a, 
   float2* const pkb = d.pk;
   float2* const gkb = d.gk;
   const signed char* const lut = d.lut;
-#if HMC_LDS_TAB
-  // per-shell float tables of the chain in LDS (indexed gathers stay on chip)
-  __shared__ float stf[4 * kMaxBins];
-  for (int i = tid; i < 4 * kMaxBins; i += NT) stf[i] = (i % kMaxBins) < d.nb ? gldf(d.tf + i) : 0.f;
-  __syncthreads();
-  const float* const tf = stf;
-#else
-  const float* const tf = d.tf;
-#endif
   const double* const td = d.td;
   float2* L = lds + b;
   float2 v[E];
@@ -694,20 +692,49 @@ __device__ __forceinline__ void xpass(const ChainDev& d, int lt, const XArgs a, 
 
   static_assert(F == 0 || MODE == X_FWD, "flag instantiation of X_FWD only");
   const bool dot = (MODE == X_FWD) && (F == 1 || (a.flags & XF_DOT));
+  // Every load is issued here, the chain's per-shell float tables (for LDS: indexed gathers
+  // stay on chip) ahead of the fields: one trip to memory, where tables, T and the state one
+  // after the other made three (step pass: 64^3, eight chains, 12.8 -> 11.9 us; 128^3, one
+  // chain, 13.1 -> 12.2, four 35.6 -> 34.1; 192^3, two, 61.9 -> 60.4; 256^3 68.2 -> 66.8).
+  // The state of 12 or 16 elements per thread (192^3, 256^3) costs a wave per SIMD in
+  // registers (192^3: 63.4 us): there its loads stay behind the transform.
+  constexpr bool kPre = E <= 8 && (MODE != X_FWD || F == 1);
   if (dot) bins_zero(bins);
-
+  constexpr bool kState = MODE == X_START || MODE == X_STEP || MODE == X_END;
+  __shared__ float stf[kTSize];
+  constexpr int kTabs = (kTSize + NT - 1) / NT;
+  float ltf[kTabs];
+#pragma unroll
+  for (int i = 0; i < kTabs; ++i) {
+    const int j = tid + i * NT;
+    ltf[i] = j < kTSize && (j % kMaxBins) < d.nb ? gldf(d.tf + j) : 0.f;
+  }
+  float2 dkv[MODE == X_FWD && F == 0 ? 1 : E], pkv[kState ? E : 1];
   if constexpr (MODE != X_INV) {
 #pragma unroll
     for (int e = 0; e < E; ++e) v[e] = gldi(Tb, offs(e));
-    fft<N, T, +1>(v, L, ES, t, active, tw, RL{});
   }
+  if constexpr (kPre) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      dkv[e] = xld(dkb, offs(e));
+      if constexpr (kState) pkv[e] = MODE == X_START ? gldi(gkb, offs(e)) : xld(pkb, offs(e));
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < kTabs; ++i)
+    if (tid + i * NT < kTSize) stf[tid + i * NT] = ltf[i];
+  const float* const tf = stf;
+  __syncthreads();
+  if constexpr (MODE != X_INV) fft<N, T, +1>(v, L, ES, t, active, tw, RL{});
 
   double acc0 = 0.0, acc1 = 0.0;
   if constexpr (MODE == X_INV) {
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const int me = shell(e);
-      const float2 x = gldi(dkb, offs(e));
+      if constexpr (!kPre) dkv[e] = gldi(dkb, offs(e));
+      const float2 x = dkv[e];
       float s = norm;
       if ((a.flags & XF_SCALE) && me >= 0) s *= tf[kTScale + me];
       if ((a.flags & XF_PRIOR) && me >= 0) s *= rsqrtf(tf[kTInvLam + me]);  // sqrt(lambda_m)
@@ -715,16 +742,17 @@ __device__ __forceinline__ void xpass(const ChainDev& d, int lt, const XArgs a, 
     }
   } else if constexpr (MODE == X_FWD && F == 1) {
     // every delta_hat load issued together (idle lanes read column 0, in bounds)
-    float2 xk[E];
+    if constexpr (!kPre) {
 #pragma unroll
-    for (int e = 0; e < E; ++e) xk[e] = gldi(dkb, offs(e));
+      for (int e = 0; e < E; ++e) dkv[e] = gldi(dkb, offs(e));
+    }
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       const int me = shell(e);
       const bool on = active && me >= 0;
       const float2 g = cscale(v[e], norm);
       const float sc = tf[kTScale + (me >= 0 ? me : 0)];
-      const double val = on ? wz * ((double)(sc * xk[e].x) * g.x + (double)(sc * xk[e].y) * g.y) : 0.0;
+      const double val = on ? wz * ((double)(sc * dkv[e].x) * g.x + (double)(sc * dkv[e].y) * g.y) : 0.0;
       if (on) atomicAdd(&bins[((threadIdx.x >> 6) * kBinCopies + bin_copy<B>()) * kBinStride + me], (bin_t)val);
     }
   } else if constexpr (MODE == X_FWD) {
@@ -755,13 +783,14 @@ __device__ __forceinline__ void xpass(const ChainDev& d, int lt, const XArgs a, 
   } else {
     // X_START, X_STEP, X_END: kick (and drift).  All loads of the elements are
     // issued before the first use.
-    float2 dkv[E], pkv[E];
     int m[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
       m[e] = shell(e);
-      dkv[e] = xld(dkb, offs(e));
-      pkv[e] = MODE == X_START ? gldi(gkb, offs(e)) : xld(pkb, offs(e));  // X_START: g_hat
+      if constexpr (!kPre) {
+        dkv[e] = xld(dkb, offs(e));
+        pkv[e] = MODE == X_START ? gldi(gkb, offs(e)) : xld(pkb, offs(e));  // X_START: g_hat
+      }
     }
 #pragma unroll
     for (int e = 0; e < E; ++e) {
@@ -870,7 +899,7 @@ __global__ void __launch_bounds__((xthreads<N, P>())) k_xpass_n(const ChainDev* 
   }
   for (TileWalk w = tile_walk(total); w.cur < w.end; w.cur += w.step) {
     const int tile = w.cur;
-    const int c = find_chain(ch, nch, tile, kTileXY);
+    const int c = chain_of(nch, total, tile);
     const ChainDev& d = ch[c];
     xpass<N, MODE, P, F>(d, tile - d.tb[kTileXY], a, tw, lds, red, bins);
   }
@@ -926,7 +955,7 @@ __global__ void __launch_bounds__((xthreads<N, P>())) k_ypass_n(const ChainDev* 
   extern __shared__ float2 lds[];
   for (TileWalk w = tile_walk(total); w.cur < w.end; w.cur += w.step) {
     const int tile = w.cur;
-    const int c = find_chain(ch, nch, tile, kTileXY);
+    const int c = chain_of(nch, total, tile);
     const ChainDev& d = ch[c];
     ypass<N, DIR, P>(d, tile - d.tb[kTileXY], tw, lds, buf);
   }
@@ -1099,7 +1128,7 @@ __global__ void __launch_bounds__(kThreads) k_zpass_n(const ChainDev* __restrict
 #endif
   for (TileWalk w = tile_walk(total); w.cur < w.end; w.cur += w.step) {
     const int tile = w.cur;
-    const int c = find_chain(ch, nch, tile, kTileZ);
+    const int c = chain_of(nch, total, tile);
     const ChainDev& d = ch[c];
 #if HMC_ZTWL
     zpass_t<N, MODE, P>(d, tile - d.tb[kTileZ], a, stw, stw + N / 2, lds, red);
@@ -1194,7 +1223,7 @@ __device__ __forceinline__ void static_for(F&& f) {
 // compiled without those branches (straight-line z-row code, no spilled registers)
 template <int N, bool FULL>
 __device__ __forceinline__ void yzpass(const ChainDev& d, int x, const ZArgs a, float2* lds,
-                                       const float2* stw, double* red) {
+                                       float2* stw, const float2* __restrict__ tw, double* red) {
   using C = PC<N>;
   using L = PL<N>;
   constexpr int M = N / 2, H = M + 1;
@@ -1236,6 +1265,15 @@ __device__ __forceinline__ void yzpass(const ChainDev& d, int x, const ZArgs a, 
   // column 0 of group 0 carries kz = 0 and kz = M: Z = C_0 + i C_M.  The kz = M
   // values are loaded first, so that waiting for them does not wait for the rest
   // of the plane (loads complete in order)
+  // The twiddles' loads go ahead of the plane's (they reach LDS while the plane arrives).
+  constexpr int kTws = (2 * N + P - 1) / P;
+  float2 ltw[kTws];
+#pragma unroll
+  for (int j = 0; j < kTws; ++j) {
+    const int i = tid + j * P;
+    if (i < 2 * N)
+      ltw[j] = i < N / 2 ? tw[tw_offset(N / 2) + i] : i < N ? tw[tw_offset(N) + i - N / 2] : tw[tw_offset(N) + i - N];
+  }
   float2 cm[EY];
   if (b == 0) {
 #pragma unroll
@@ -1249,6 +1287,10 @@ __device__ __forceinline__ void yzpass(const ChainDev& d, int x, const ZArgs a, 
       const float2 val = gldi(at(g, e), toff);
       if (g < GR) v[g < GR ? g : 0][e] = val; else u[g < GR ? 0 : g - GR][e] = val;
     }
+#pragma unroll
+  for (int j = 0; j < kTws; ++j)
+    if (tid + j * P < 2 * N) stw[tid + j * P] = ltw[j];
+  __syncthreads();
   if (b == 0) {
 #pragma unroll
     for (int e = 0; e < EY; ++e) v[0][e] = make_float2(v[0][e].x - cm[e].y, v[0][e].y + cm[e].x);
@@ -1388,10 +1430,7 @@ __global__ void __launch_bounds__(PC<N>::P) k_yzpass_n(const ChainDev* __restric
   __shared__ float2 lds[PL<N>::TOTAL];
   __shared__ float2 stw[2 * N];
   __shared__ double red[PC<N>::P / 64];
-  for (int i = threadIdx.x; i < 2 * N; i += PC<N>::P)
-    stw[i] = i < N / 2 ? tw[tw_offset(N / 2) + i] : i < N ? tw[tw_offset(N) + i - N / 2] : tw[tw_offset(N) + i - N];
-  __syncthreads();
-  yzpass<N, FULL>(ch[blockIdx.x / N], (int)(blockIdx.x % N), a, lds, stw, red);
+  yzpass<N, FULL>(ch[blockIdx.x / N], (int)(blockIdx.x % N), a, lds, stw, tw, red);
 }
 
 bool plane_pass_supported(int n) { return n == 64 || n == 128 || n == 192 || n == 256; }
@@ -1675,7 +1714,7 @@ __global__ void __launch_bounds__(kThreads) k_xpass_l_n(const ChainDev* __restri
   extern __shared__ float2 lds[];
   __shared__ double red[4];
   for (TileWalk w = tile_walk(total); w.cur < w.end; w.cur += w.step) {
-    const ChainDev& d = ch[find_chain(ch, nch, w.cur, kTileXY)];
+    const ChainDev& d = ch[chain_of(nch, total, w.cur)];
     xpass_l<N, MODE>(d, w.cur - d.tb[kTileXY], a, tw, lds, red);
   }
 }
@@ -1686,7 +1725,7 @@ __global__ void __launch_bounds__(kThreads) k_zpass_l_n(const ChainDev* __restri
   extern __shared__ float2 lds[];
   __shared__ double red[4];
   for (TileWalk w = tile_walk(total); w.cur < w.end; w.cur += w.step) {
-    const ChainDev& d = ch[find_chain(ch, nch, w.cur, kTileZ)];
+    const ChainDev& d = ch[chain_of(nch, total, w.cur)];
     zpass_l<N, MODE>(d, w.cur - d.tb[kTileZ], a, tw, lds, red);
   }
 }
