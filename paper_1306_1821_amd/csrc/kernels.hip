@@ -1159,7 +1159,8 @@ __global__ void __launch_bounds__(kThreads) k_zpass_n(const ChainDev* __restrict
 // transform: A_k = (Z_k + conj Z_{-k}) / 2, B_k = -i (Z_k - conj Z_{-k}) / 2.
 template <int N> struct PC;
 template <> struct PC<256> {
-  static constexpr int P = 512;          // threads per workgroup
+  static constexpr int P = 512;          // threads per plane
+  static constexpr int PP = 1;           // planes per workgroup
   static constexpr int TY = 16;          // threads per y pencil (cyclic, 16 values each)
   using RLY = Radices<16, 16>;
   static constexpr int TZ = 16;          // threads per z row (cyclic, 8 values each)
@@ -1170,17 +1171,30 @@ template <> struct PC<256> {
 // each, no group in LDS); radix-12 pencils, 8-thread z rows of the 96-point
 // half-length transform (12 values each)
 template <> struct PC<192> {
-  static constexpr int P = 512;
+  static constexpr int P = 512, PP = 1;
   static constexpr int TY = 16;          // 12 values each
   using RLY = Radices<4, 4, 12>;
   static constexpr int TZ = 8;           // 12 values each
   using RLZ = Radices<4, 4, 6>;
   static constexpr int GL = 0;
 };
+// 32^3: the plane (32 x 17 complex, 4 KB) in registers of 128 threads (4 values each, one
+// pencil group, one z chunk); two planes per workgroup, as a real-space tile has 64 rows.
+// Single-size contexts only: in a batch of several sizes, one launch per size then stays bit
+// for bit the launch over the whole batch.  Four chains: 5.4 us for the y, z, y passes' 11.5
+// us and two launch gaps (a sweep without the joint move 629 -> 434 us).
+template <> struct PC<32> {
+  static constexpr int P = 128, PP = 2;
+  static constexpr int TY = 8;           // 4 values each
+  using RLY = Radices<4, 4, 2>;
+  static constexpr int TZ = 4;           // 4 values each
+  using RLZ = Radices<4, 4>;
+  static constexpr int GL = 0;
+};
 // 64^3: the plane (64 x 33 complex, 17 KB) in registers of 256 threads (8 values
 // each, one pencil group, one z chunk); 4-thread z rows of the 32-point transform
 template <> struct PC<64> {
-  static constexpr int P = 256;
+  static constexpr int P = 256, PP = 1;
   static constexpr int TY = 8;           // 8 values each
   using RLY = Radices<8, 8>;
   static constexpr int TZ = 4;           // 8 values each
@@ -1190,7 +1204,7 @@ template <> struct PC<64> {
 // 128^3: the plane (128 x 65 complex, 66 KB) in registers of 512 threads (16 values
 // each, no group in LDS); 8-thread z rows of the 64-point half-length transform
 template <> struct PC<128> {
-  static constexpr int P = 512;
+  static constexpr int P = 512, PP = 1;
   static constexpr int TY = 16;          // 8 values each
   using RLY = Radices<8, 4, 4>;
   static constexpr int TZ = 8;           // 8 values each
@@ -1234,10 +1248,10 @@ __device__ __forceinline__ void yzpass(const ChainDev& d, int x, const ZArgs a, 
   static_assert(M % PY == 0 && N % RZ == 0 && RZ % TY == 0 && EY % EC == 0, "plane tiling");
   static_assert(64 % TZ == 0 && TZ <= 16, "a z row sits in one DPP row group of a wavefront");
   static_assert(CR % TZ == 0 && GR >= 1, "register / LDS column split on a row-thread boundary");
-  // the plane's data energy goes to its own real-space tiles: a plane must cover whole
-  // tiles of the real-space pass (at 32^3 and below one tile spans several planes)
-  static_assert(N % ZC<N>::B == 0, "a plane covers whole real-space tiles");
-  const int tid = threadIdx.x;
+  // the data energy of a workgroup's planes goes to their own real-space tiles: they must
+  // cover whole tiles of the real-space pass (at 16^3 and below one tile spans many planes)
+  static_assert(C::PP * N % ZC<N>::B == 0, "a workgroup's planes cover whole real-space tiles");
+  const int tid = threadIdx.x % P;
   const int b = tid % PY, t = tid / PY;   // column phase: pencil b of each group, its thread t
   const int r = tid / TZ, tz = tid % TZ;  // row phase: row r of the chunk, its thread tz
   // twiddles staged in LDS: W_M^i (i < M), W_N^k (k < M), then W_N^i (i < N) for the
@@ -1416,30 +1430,35 @@ __device__ __forceinline__ void yzpass(const ChainDev& d, int x, const ZArgs a, 
     }
   });
   if (data) {
-    // the plane's data energy into the first of its z-pass tiles, zeros into the others
-    constexpr int tpp = N / ZC<N>::B;
-    const double sd = block_sum_w<P / 64>(dat, red);
-    if (tid < tpp) d.part[kPartDat * d.maxtiles + x * tpp + tid] = tid == 0 ? sd : 0.0;
+    // the workgroup's data energy into the first of its z-pass tiles, zeros into the others
+    constexpr int tpp = C::PP * N / ZC<N>::B;
+    const int i = threadIdx.x;
+    const double sd = block_sum_w<C::PP * P / 64>(dat, red);
+    if (i < tpp) d.part[kPartDat * d.maxtiles + x / C::PP * tpp + i] = i == 0 ? sd : 0.0;
   }
 }
 
-// single-size launch: N consecutive workgroups per chain, one per x plane
+// single-size launch: N / PP consecutive workgroups per chain, PP x planes each
 template <int N, bool FULL>
-__global__ void __launch_bounds__(PC<N>::P) k_yzpass_n(const ChainDev* __restrict__ ch, ZArgs a,
-                                                        const float2* __restrict__ tw) {
-  __shared__ float2 lds[PL<N>::TOTAL];
+__global__ void __launch_bounds__(PC<N>::P * PC<N>::PP) k_yzpass_n(const ChainDev* __restrict__ ch, ZArgs a,
+                                                                    const float2* __restrict__ tw) {
+  constexpr int PP = PC<N>::PP, W = N / PP;
+  __shared__ float2 lds[PP][PL<N>::TOTAL];
   __shared__ float2 stw[2 * N];
-  __shared__ double red[PC<N>::P / 64];
-  yzpass<N, FULL>(ch[blockIdx.x / N], (int)(blockIdx.x % N), a, lds, stw, tw, red);
+  __shared__ double red[PP * PC<N>::P / 64];
+  const int h = PP == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / PC<N>::P);  // whole waves
+  yzpass<N, FULL>(ch[blockIdx.x / W], (int)(blockIdx.x % W) * PP + h, a, lds[h], stw, tw, red);
 }
 
-bool plane_pass_supported(int n) { return n == 64 || n == 128 || n == 192 || n == 256; }
+bool plane_pass_supported(int n) { return n == 32 || plane_pass_batches(n); }
+bool plane_pass_batches(int n) { return n == 64 || n == 128 || n == 192 || n == 256; }
 template <int N>
 static void launch_yz_n(const ChainDev* ch, int nch, ZArgs a, const float2* tw, hipStream_t s) {
+  const dim3 g(nch * (N / PC<N>::PP)), b(PC<N>::P * PC<N>::PP);
   if (a.flags & (ZF_DATA | ZF_WRITE_DR | ZF_WRITE_DRN))
-    hipLaunchKernelGGL((k_yzpass_n<N, true>), dim3(nch * N), dim3(PC<N>::P), 0, s, ch, a, tw);
+    hipLaunchKernelGGL((k_yzpass_n<N, true>), g, b, 0, s, ch, a, tw);
   else
-    hipLaunchKernelGGL((k_yzpass_n<N, false>), dim3(nch * N), dim3(PC<N>::P), 0, s, ch, a, tw);
+    hipLaunchKernelGGL((k_yzpass_n<N, false>), g, b, 0, s, ch, a, tw);
 }
 void launch_yzpass(const ChainDev* ch, int nch, ZArgs a, const float2* tw, hipStream_t s, int n) {
   switch (n) {
@@ -1447,6 +1466,7 @@ void launch_yzpass(const ChainDev* ch, int nch, ZArgs a, const float2* tw, hipSt
     case 192: launch_yz_n<192>(ch, nch, a, tw, s); break;
     case 128: launch_yz_n<128>(ch, nch, a, tw, s); break;
     case 64: launch_yz_n<64>(ch, nch, a, tw, s); break;
+    case 32: launch_yz_n<32>(ch, nch, a, tw, s); break;
     default: break;
   }
 }

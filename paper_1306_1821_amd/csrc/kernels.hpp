@@ -67,7 +67,8 @@ void launch_mass_prep(int phase, const ChainDev* ch, int total_r, const float* l
                       hipStream_t s);
 // y-z plane pass (inverse y, C2R z, data force, R2C z, forward y in one kernel)
 // for single-size launches of the grid sizes it supports
-bool plane_pass_supported(int n);
+bool plane_pass_supported(int n);  // contexts of one grid size
+bool plane_pass_batches(int n);    // size groups of a batch
 void launch_yzpass(const ChainDev* ch, int nch, ZArgs a, const float2* tw, hipStream_t s, int n);
 // grids whose trajectories and joint moves run in one workgroup per chain (single-size
 // contexts); launch_small_joint follows launch_rj(RJ_BEGIN)

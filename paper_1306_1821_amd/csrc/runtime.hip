@@ -270,11 +270,11 @@ struct Seq {
       return;
     }
     bool some = false;
-    for (auto& g : c->groups) some |= plane_pass_supported(g.n);
+    for (auto& g : c->groups) some |= plane_pass_batches(g.n);
     if (c->plane_pass && un == 0 && c->grouped[1] && c->grouped[2] && some) {
       Timed tm(c, 2, s);
       for (auto& g : c->groups) {
-        if (plane_pass_supported(g.n)) {
+        if (plane_pass_batches(g.n)) {
           launch_yzpass(g.d, g.nch, za, c->tw, s, g.n);
         } else {
           launch_ypass(-1, g.d, g.nch, g.total[kTileXY], c->lds_x, c->tw, 0, s, g.n, 0, c->plan[1]);
@@ -1132,7 +1132,7 @@ hmc_status hmc_autotune(hmc_ctx* c, int32_t reps, int32_t* chosen) {
   // batches whose size groups have a fused plane pass run it only when the y and
   // real-space classes launch per size group, so those classes keep that launch
   bool plane_groups = false;
-  for (auto& g : c->groups) plane_groups |= plane_pass_supported(g.n);
+  for (auto& g : c->groups) plane_groups |= plane_pass_batches(g.n);
   plane_groups &= c->plane_pass && c->uniform_n == 0;
   for (int cls = 0; cls < 3 && st == HMC_OK; ++cls) {
     float best = 0.f;
