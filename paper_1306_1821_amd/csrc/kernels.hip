@@ -1211,6 +1211,8 @@ template <> struct PC<128> {
   using RLZ = Radices<8, 8>;
   static constexpr int GL = 0;
 };
+constexpr bool has_plane(int n) { return n == 32 || n == 64 || n == 128 || n == 192 || n == 256; }
+constexpr int plane_groups(int n) { return n == 32 ? n / PC<32>::PP : n; }  // workgroups per chain
 // LDS layout in float2: [0, A) the y-transform exchange and the z-row chunk buffer
 // (used in turn), [A, A + N LS) the columns kept in LDS (row-major, stride LS),
 // then N values for separating column 0
@@ -1234,8 +1236,14 @@ __device__ __forceinline__ void static_for(F&& f) {
 }
 
 // FULL = false: the plain leapfrog step's launch (no data energy, no real field out),
-// compiled without those branches (straight-line z-row code, no spilled registers)
-template <int N, bool FULL>
+// compiled without those branches (straight-line z-row code, no spilled registers).
+// KIND: the plain data force, or a pass of the learned mass (see below):
+//   YZ_VEL    T2: real space times D^(1/2) and back;
+//   YZ_PRIOR  T3 to real space, less beta, each row in place of its transform (pairs [y][n],
+//             n < N/2, at the row stride of T3); nothing goes back;
+//   YZ_FORCE  T with YZ_PRIOR's field h: D^(1/2) (alpha delta + h), and its unweighted sum
+//             per workgroup.
+template <int N, bool FULL, int KIND>
 __device__ __forceinline__ void yzpass(const ChainDev& d, int x, const ZArgs a, float2* lds,
                                        float2* stw, const float2* __restrict__ tw, double* red) {
   using C = PC<N>;
@@ -1264,7 +1272,8 @@ __device__ __forceinline__ void yzpass(const ChainDev& d, int x, const ZArgs a, 
   float2* const Ls = lds + L::A;          // columns CR .. M-1, [y][c - CR]
   // addresses: a uniform (scalar) base per element plus one per-thread offset, so
   // that the loads and stores of the plane share a single offset register
-  float2* const Pl = d.T + (size_t)x * (N * H);
+  constexpr bool LEARN = KIND == YZ_VEL || KIND == YZ_FORCE;
+  float2* const Pl = (KIND == YZ_VEL ? d.T2 : KIND == YZ_PRIOR ? d.T3 : d.T) + (size_t)x * (N * H);
   const uint32_t toff = (uint32_t)(t * H + b);
   auto at = [&](int g, int e) {
     // the row base is pinned in scalar registers: left to itself the compiler folds
@@ -1328,22 +1337,23 @@ __device__ __forceinline__ void yzpass(const ChainDev& d, int x, const ZArgs a, 
                                             : nullptr;
   const bool data = FULL && (a.flags & ZF_DATA);
   float2* const Lr = lds + r * RSZ;  // this thread's row of the chunk buffer
-  double dat = 0.0;
+  double dat = 0.0, sum = 0.0;
   // alpha and beta of chunk q + 1 are loaded as soon as chunk q's force is formed,
   // so that they arrive while chunk q finishes its transforms
-  float2 al[EZ], be[EZ];
-  auto load_ab = [&](int q) {
-    const size_t rq = ((size_t)x * N + q * RZ) * M;  // the chunk's first voxel pair (uniform)
-    const float2* ab = ap + rq;
-    const float2* bb = bp + rq;
-    asm volatile("" : "+s"(ab), "+s"(bb));  // scalar bases, one offset register (see at())
+  float2 al[EZ], be[EZ], sm[EZ], fp[EZ];
+  // chunk q of a real field, pairs at row stride `rs` (scalar base, one offset register: see at())
+  auto load_row = [&](float2* v, const float2* f, int rs, int q, bool stream) {
+    f += ((size_t)x * N + q * RZ) * rs;
+    asm volatile("" : "+s"(f));
 #pragma unroll
-    for (int e = 0; e < EZ; ++e) {
-      al[e] = ld_si(ab + TZ * e, (uint32_t)(r * M + tz));
-      be[e] = ld_si(bb + TZ * e, (uint32_t)(r * M + tz));
-    }
+    for (int e = 0; e < EZ; ++e)
+      v[e] = stream ? ld_si(f + TZ * e, (uint32_t)(r * rs + tz)) : gldi(f + TZ * e, (uint32_t)(r * rs + tz));
   };
-  load_ab(0);
+  auto load_ab = [&](int q) {
+    if constexpr (KIND == YZ_DATA || KIND == YZ_FORCE) load_row(al, ap, M, q, true);
+    if constexpr (KIND == YZ_DATA || KIND == YZ_PRIOR || (KIND == YZ_FORCE && FULL)) load_row(be, bp, M, q, true);
+  };
+  if constexpr (KIND != YZ_FORCE) load_ab(0);
   static_for<0, NCH>([&](auto qc) {
     constexpr int q = decltype(qc)::value;
     const size_t rq = ((size_t)x * N + q * RZ) * M;   // the chunk's first voxel pair (uniform)
@@ -1355,6 +1365,7 @@ __device__ __forceinline__ void yzpass(const ChainDev& d, int x, const ZArgs a, 
 #pragma unroll
       for (int j = 0; j < EC; ++j) lds[(t + TY * j) * RSZ + g * PY + b] = v[g][EC * q + j];
     __syncthreads();
+    if constexpr (KIND == YZ_FORCE) load_ab(q);  // four fields a chunk: no registers to hold the next one's
     float2 xr[EZ + 1], w[EZ];
 #pragma unroll
     for (int e = 0; e < EZ; ++e) {
@@ -1363,15 +1374,30 @@ __device__ __forceinline__ void yzpass(const ChainDev& d, int x, const ZArgs a, 
     }
     xr[EZ] = make_float2(xr[0].y, 0.f);  // lane 0: X_M from the packed column (X_0 = Re xr[0])
     c2r_pre<N, TZ, EZ>(xr, w, Lr, tz, twN);
+    if constexpr (LEARN) load_row(sm, reinterpret_cast<const float2*>(d.smass), M, q, false);
+    if constexpr (KIND == YZ_FORCE) load_row(fp, d.T3, H, q, false);
     zfft<M, TZ, -1, typename C::RLZ>(w, Lr, tz, true, twM);
 #pragma unroll
     for (int e = 0; e < EZ; ++e) {
       const float2 xv = w[e];
+      if constexpr (KIND == YZ_PRIOR) {
+        gsti(Pl + (size_t)q * RZ * H + TZ * e, (uint32_t)(r * H + tz), csub(xv, be[e]));
+        continue;
+      }
       if (FULL && drout) gsti(reinterpret_cast<float2*>(drout) + rq + TZ * e, ro, xv);  // trajectory ends
       if (data) dat += voxel_energy(al[e], xv, be[e]);
-      w[e] = data_force(al[e], xv, be[e]);
+      if constexpr (KIND == YZ_DATA) {
+        w[e] = data_force(al[e], xv, be[e]);
+      } else if constexpr (KIND == YZ_VEL) {
+        w[e] = make_float2(sm[e].x * xv.x, sm[e].y * xv.y);
+      } else {
+        const float2 g = make_float2(__builtin_fmaf(al[e].x, xv.x, fp[e].x), __builtin_fmaf(al[e].y, xv.y, fp[e].y));
+        sum += (double)g.x + (double)g.y;
+        w[e] = make_float2(sm[e].x * g.x, sm[e].y * g.y);
+      }
     }
-    if constexpr (q + 1 < NCH) load_ab(q + 1);
+    if constexpr (q + 1 < NCH && KIND != YZ_FORCE) load_ab(q + 1);
+    if constexpr (KIND == YZ_PRIOR) return;
     zfft<M, TZ, +1, typename C::RLZ>(w, Lr, tz, true, twM);
     float x0 = 0.f;
     r2c_post<N, TZ, EZ>(w, Lr, tz, true, twN, [&](int k, float2 X) {
@@ -1390,6 +1416,7 @@ __device__ __forceinline__ void yzpass(const ChainDev& d, int x, const ZArgs a, 
 #pragma unroll
       for (int j = 0; j < EC; ++j) v[g][EC * q + j] = lds[(t + TY * j) * RSZ + g * PY + b];
   });
+  if constexpr (KIND == YZ_PRIOR) return;
   __syncthreads();
   // forward y transforms, each group stored as soon as it is done (the stores drain
   // while the next group transforms); column 0 of group 0 is separated first
@@ -1436,37 +1463,56 @@ __device__ __forceinline__ void yzpass(const ChainDev& d, int x, const ZArgs a, 
     const double sd = block_sum_w<C::PP * P / 64>(dat, red);
     if (i < tpp) d.part[kPartDat * d.maxtiles + x / C::PP * tpp + i] = i == 0 ? sd : 0.0;
   }
+  if constexpr (KIND == YZ_FORCE) {  // the sum of the workgroup's planes
+    const double sg = block_sum_w<C::PP * P / 64>(sum, red);
+    if (threadIdx.x == 0) d.part[kPartAux * d.maxtiles + x / C::PP] = sg;
+  }
 }
 
 // single-size launch: N / PP consecutive workgroups per chain, PP x planes each
-template <int N, bool FULL>
-__global__ void __launch_bounds__(PC<N>::P * PC<N>::PP) k_yzpass_n(const ChainDev* __restrict__ ch, ZArgs a,
+// At 128^3 the register cap puts two workgroups on a compute unit, one's memory phases over
+// the other's transforms (four chains: learned force 40.5 -> 35.5 us, data force with the energy
+// 45.1 -> 38.6; the learned force's energy instantiation spills under it and goes without)
+template <int N, bool FULL, int KIND>
+constexpr int yz_waves() { return N == 128 && !(FULL && KIND == YZ_FORCE) ? 4 : 1; }
+template <int N, bool FULL, int KIND = YZ_DATA>
+__global__ void __launch_bounds__(PC<N>::P * PC<N>::PP, (yz_waves<N, FULL, KIND>())) k_yzpass_n(const ChainDev* __restrict__ ch, ZArgs a,
                                                                     const float2* __restrict__ tw) {
   constexpr int PP = PC<N>::PP, W = N / PP;
   __shared__ float2 lds[PP][PL<N>::TOTAL];
   __shared__ float2 stw[2 * N];
   __shared__ double red[PP * PC<N>::P / 64];
   const int h = PP == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / PC<N>::P);  // whole waves
-  yzpass<N, FULL>(ch[blockIdx.x / W], (int)(blockIdx.x % W) * PP + h, a, lds[h], stw, tw, red);
+  yzpass<N, FULL, KIND>(ch[blockIdx.x / W], (int)(blockIdx.x % W) * PP + h, a, lds[h], stw, tw, red);
 }
 
-bool plane_pass_supported(int n) { return n == 32 || plane_pass_batches(n); }
+bool plane_pass_supported(int n) { return has_plane(n); }
 bool plane_pass_batches(int n) { return n == 64 || n == 128 || n == 192 || n == 256; }
 template <int N>
-static void launch_yz_n(const ChainDev* ch, int nch, ZArgs a, const float2* tw, hipStream_t s) {
+static void launch_yz_n(const ChainDev* ch, int nch, ZArgs a, const float2* tw, hipStream_t s, int kind) {
   const dim3 g(nch * (N / PC<N>::PP)), b(PC<N>::P * PC<N>::PP);
-  if (a.flags & (ZF_DATA | ZF_WRITE_DR | ZF_WRITE_DRN))
+  const bool full = a.flags & (ZF_DATA | ZF_WRITE_DR | ZF_WRITE_DRN);
+  if (kind == YZ_VEL)
+    hipLaunchKernelGGL((k_yzpass_n<N, false, YZ_VEL>), g, b, 0, s, ch, a, tw);
+  else if (kind == YZ_PRIOR)
+    hipLaunchKernelGGL((k_yzpass_n<N, false, YZ_PRIOR>), g, b, 0, s, ch, a, tw);
+  else if (kind == YZ_FORCE && full)
+    hipLaunchKernelGGL((k_yzpass_n<N, true, YZ_FORCE>), g, b, 0, s, ch, a, tw);
+  else if (kind == YZ_FORCE)
+    hipLaunchKernelGGL((k_yzpass_n<N, false, YZ_FORCE>), g, b, 0, s, ch, a, tw);
+  else if (full)
     hipLaunchKernelGGL((k_yzpass_n<N, true>), g, b, 0, s, ch, a, tw);
   else
     hipLaunchKernelGGL((k_yzpass_n<N, false>), g, b, 0, s, ch, a, tw);
 }
-void launch_yzpass(const ChainDev* ch, int nch, ZArgs a, const float2* tw, hipStream_t s, int n) {
+void launch_yzpass(const ChainDev* ch, int nch, ZArgs a, const float2* tw, hipStream_t s, int n,
+                   int kind) {
   switch (n) {
-    case 256: launch_yz_n<256>(ch, nch, a, tw, s); break;
-    case 192: launch_yz_n<192>(ch, nch, a, tw, s); break;
-    case 128: launch_yz_n<128>(ch, nch, a, tw, s); break;
-    case 64: launch_yz_n<64>(ch, nch, a, tw, s); break;
-    case 32: launch_yz_n<32>(ch, nch, a, tw, s); break;
+    case 256: launch_yz_n<256>(ch, nch, a, tw, s, kind); break;
+    case 192: launch_yz_n<192>(ch, nch, a, tw, s, kind); break;
+    case 128: launch_yz_n<128>(ch, nch, a, tw, s, kind); break;
+    case 64: launch_yz_n<64>(ch, nch, a, tw, s, kind); break;
+    case 32: launch_yz_n<32>(ch, nch, a, tw, s, kind); break;
     default: break;
   }
 }
@@ -1480,7 +1526,11 @@ void launch_yzpass(const ChainDev* ch, int nch, ZArgs a, const float2* tw, hipSt
 // real-space pass partials and F(D^(1/2)) precomputed.  A step is
 //   x L_DRIFT (T2 -> drift -> delta_hat, inverse x of delta_hat -> T and of
 //   delta_hat/lambda -> T3), y-1 T, y-1 T3, z LZ_FORCE (T, T3 -> T), y+1 T,
-//   x L_KICK (T -> kick -> inverse x of p_hat/m -> T2), y-1 T2, z LZ_VEL, y+1 T2.
+//   x L_KICK (T -> kick -> inverse x of p_hat/m -> T2), y-1 T2, z LZ_VEL, y+1 T2,
+// and a launch that reduces mean(g); contexts with a plane pass take the two real-space
+// parts as YZ_PRIOR and YZ_FORCE and as YZ_VEL, T, T2 and T3 one round trip each, and the
+// kick sums the planes' g itself: 5 launches instead of 10 (trajectory of 20 steps: 128^3,
+// four chains, 4.37 -> 3.69 ms; 64^3, eight, 1.83 -> 1.33; 256^3 9.63 -> 8.25).
 
 // C2R of one half-complex row into v (v[e] = (x_2n, x_2n+1), n = t + T e).
 template <int N>
@@ -1587,9 +1637,13 @@ __device__ __forceinline__ void xpass_l(const ChainDev& d, int lt, const XArgs a
   const float norm = d.norm;
   const float kick = a.kick * d.eps, drift = a.drift * d.eps;
   constexpr bool KICK = MODE == L_KICK || MODE == L_KICK_LAST;
-  __shared__ float stf[4 * kMaxBins];
-  for (int i = tid; i < 4 * kMaxBins; i += kThreads) stf[i] = (i % kMaxBins) < d.nb ? gldf(d.tf + i) : 0.f;
-  __syncthreads();
+  __shared__ float stf[kTSize];  // written while the fields' loads are in flight (see xpass)
+  float ltf[kTSize / kThreads];
+#pragma unroll
+  for (int i = 0; i < kTSize / kThreads; ++i) {
+    const int j = tid + i * kThreads;
+    ltf[i] = (j % kMaxBins) < d.nb ? gldf(d.tf + j) : 0.f;
+  }
   const float* const tf = stf;
   const double* const td = d.td;
   constexpr uint32_t qmax = 3u * (N / 2) * (N / 2);
@@ -1608,8 +1662,23 @@ __device__ __forceinline__ void xpass_l(const ChainDev& d, int lt, const XArgs a
     w[e] = KICK ? gldi(d.shat, offs(e)) : MODE == L_START ? gldi(d.gk, offs(e))
                                                           : make_float2(0.f, 0.f);
   }
+#pragma unroll
+  for (int i = 0; i < kTSize / kThreads; ++i) stf[tid + i * kThreads] = ltf[i];
+  __syncthreads();
+  double psum = 0.0;
+  if constexpr (KICK && has_plane(N)) {
+    if ((a.flags & XF_PLANES) && tid < plane_groups(N)) psum = gldd(d.part + kPartAux * d.maxtiles + tid);
+  }
   fft<N, T, +1>(v, L, ES, t, active, tw, typename C::RL{});
-  const float gbar = KICK ? (float)d.P[kGbar] : 0.f;
+  // mean of the force: reduced by a launch, or (XF_PLANES) summed here from the plane
+  // pass's sums, at most one per thread
+  float gbar = 0.f;
+  if constexpr (KICK) {
+    if (a.flags & XF_PLANES)
+      gbar = (float)(block_sum(psum, red) / (double)d.nv);
+    else
+      gbar = (float)d.P[kGbar];
+  }
   double acc0 = 0.0, acc1 = 0.0;
   const float2 z2 = make_float2(0.f, 0.f);
 #pragma unroll

@@ -18,10 +18,13 @@ enum XFlag : int {
   XF_NOSTORE = 16,  // X_FWD: do not store
   XF_OUT_SHAT = 32,  // X_FWD: store into the learned-mass transform F(D^(1/2))
   XF_PRIOR = 64,     // X_INV: scale delta_hat by sqrt(lambda_k) (prior draw)
+  XF_PLANES = 128,   // learned kick: mean force from the plane pass's sums
 };
 // learned-mass passes
 enum LMode : int { L_START = 0, L_DRIFT = 1, L_KICK = 2, L_KICK_LAST = 3 };
 enum LZMode : int { LZ_FORCE = 0, LZ_VEL = 1 };
+// y-z plane pass: the data force of a plain step, or a pass of a learned-mass step
+enum YzKind : int { YZ_DATA = 0, YZ_VEL = 1, YZ_PRIOR = 2, YZ_FORCE = 3 };
 // z-pass modes (real-space side)
 enum ZMode : int { Z_GRAD = 0, Z_NOISE = 1, Z_C2R = 2, Z_R2C = 3 };
 enum ZFlag : int {
@@ -69,7 +72,8 @@ void launch_mass_prep(int phase, const ChainDev* ch, int total_r, const float* l
 // for single-size launches of the grid sizes it supports
 bool plane_pass_supported(int n);  // contexts of one grid size
 bool plane_pass_batches(int n);    // size groups of a batch
-void launch_yzpass(const ChainDev* ch, int nch, ZArgs a, const float2* tw, hipStream_t s, int n);
+void launch_yzpass(const ChainDev* ch, int nch, ZArgs a, const float2* tw, hipStream_t s, int n,
+                   int kind = YZ_DATA);
 // grids whose trajectories and joint moves run in one workgroup per chain (single-size
 // contexts); launch_small_joint follows launch_rj(RJ_BEGIN)
 bool small_grid_supported(int n);

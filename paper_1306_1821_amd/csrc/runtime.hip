@@ -233,10 +233,10 @@ struct Seq {
     });
     tm.done(s);
   }
-  void xl(int mode, float kick, float drift) {
+  void xl(int mode, float kick, float drift, int flags = 0) {
     Timed tm(c, 3, s);
     each(0, [&](const ChainDev* dd, int n, const int* t, int u, int g) {
-      launch_xpass_learned(mode, dd, n, t[kTileXY], c->lds_x, XArgs{kick, drift, 0}, c->tw, g,
+      launch_xpass_learned(mode, dd, n, t[kTileXY], c->lds_x, XArgs{kick, drift, flags}, c->tw, g,
                            s, u);
     });
     tm.done(s);
@@ -263,7 +263,7 @@ struct Seq {
   // passes run one launch per size group), else three passes
   void yz(int zflags) {
     const ZArgs za{zflags, 0, nullptr};
-    if (c->plane_pass && un != 0 && plane_pass_supported(un)) {
+    if (planes()) {
       Timed tm(c, 2, s);
       launch_yzpass(d, nch, za, c->tw, s, un);
       tm.done(s);
@@ -289,6 +289,12 @@ struct Seq {
     y(-1);
     z(Z_GRAD, zflags);
     y(+1);
+  }
+  bool planes() const { return c->plane_pass && un != 0 && plane_pass_supported(un); }
+  void yzl(int kind, int zflags) {
+    Timed tm(c, 3, s);
+    launch_yzpass(d, nch, ZArgs{zflags, 0, nullptr}, c->tw, s, un, kind);
+    tm.done(s);
   }
   // g_hat, delta and the data energy of the current delta_hat
   void gradient(int zflags, int xflags) {
@@ -672,7 +678,16 @@ hmc_status hmc_init(const hmc_config* cfg, const hmc_buffers* buf, const double*
 static hmc_status run_trajectory_learned(hmc_ctx* c) {
   Seq q = seq_all(c);
   const int nch = (int)c->ch.size();
+  // the plane passes where the context has them (T, T2, T3 one round trip each), else the
+  // separate y, z, y passes
+  const bool planes = q.planes();
+  const int kflags = planes ? XF_PLANES : 0;
   auto force = [&](int zflags) {
+    if (planes) {
+      q.yzl(YZ_PRIOR, 0);
+      q.yzl(YZ_FORCE, zflags);
+      return;
+    }
     q.y(-1, 0);
     q.y(-1, 2);
     q.zl(LZ_FORCE, zflags);
@@ -685,15 +700,19 @@ static hmc_status run_trajectory_learned(hmc_ctx* c) {
   launch_reduce_slot(c->d_all, nch, kPartKin, kK0, kTileXY, c->stream);
   launch_reduce_slot(c->d_all, nch, kPartPri, kPi0, kTileXY, c->stream);
   force(0);
-  q.xl(L_KICK, 0.5f, 0.f);
+  q.xl(L_KICK, 0.5f, 0.f, kflags);
   for (int s = 1; s <= c->cur_steps; ++s) {
     const bool last = s == c->cur_steps;
-    q.y(-1, 1);
-    q.zl(LZ_VEL, 0);
-    q.y(+1, 1);
+    if (planes) {
+      q.yzl(YZ_VEL, 0);
+    } else {
+      q.y(-1, 1);
+      q.zl(LZ_VEL, 0);
+      q.y(+1, 1);
+    }
     q.xl(L_DRIFT, 0.f, 1.f);
     force(last ? (ZF_WRITE_DRN | ZF_DATA) : 0);
-    q.xl(last ? L_KICK_LAST : L_KICK, last ? 0.5f : 1.f, 0.f);
+    q.xl(last ? L_KICK_LAST : L_KICK, last ? 0.5f : 1.f, 0.f, kflags);
   }
   launch_reduce_slot(c->d_all, nch, kPartKin, kK1, kTileXY, c->stream);
   launch_reduce_slot(c->d_all, nch, kPartPri, kPi1, kTileXY, c->stream);
