@@ -454,14 +454,19 @@ int zpass_tiles(int n) {
 }
 
 // ------------------------------------------------------------------ helpers
+// chain of a tile: the last one whose first tile is not past it, 64 descriptors at a time
+// (a walk over them is one dependent load per chain)
 __device__ __forceinline__ int find_chain(const ChainDev* ch, int nch, int tile, int cls) {
+  if (nch == 1) return 0;
   int c = 0;
-  while (c + 1 < nch && tile >= ch[c + 1].tb[cls]) ++c;
-  return c;
+  for (int base = 0; base < nch; base += 64) {
+    const int i = base + (int)(threadIdx.x & 63);
+    c += __popcll(__ballot(i < nch && ch[i < nch ? i : 0].tb[cls] <= tile));
+  }
+  return c - 1;
 }
 
-// the same in a single-size launch: every chain has total / nch tiles (find_chain walks the
-// descriptors one dependent load after another)
+// the same in a single-size launch: every chain has total / nch tiles
 __device__ __forceinline__ int chain_of(int nch, int total, int tile) {
   return nch == 1 ? 0 : tile / (total / nch);
 }
@@ -2406,14 +2411,26 @@ __global__ void __launch_bounds__(kThreads) k_shell_index(const ChainDev* __rest
 // delta_hat per shell and take the move's g_hat and real field.
 // k-space arrays move two complex entries (16 bytes) per access: N^2 (N/2 + 1)
 // and the tile size are even
-__global__ void __launch_bounds__(kWideThreads) k_commit_k(const ChainDev* __restrict__ ch,
-                                                            int nch, int total, int what) {
+// One launch: the first total_k tiles are the k-space ones, the others the real-space ones.
+__global__ void __launch_bounds__(kWideThreads) k_commit(const ChainDev* __restrict__ ch, int nch,
+                                                          int total_k, int total, int what) {
   for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
-    const ChainDev& d = ch[find_chain(ch, nch, tile, kTileK)];
-    const int lt = tile - d.tb[kTileK];
+    const bool ks = tile < total_k;
+    const int cls = ks ? kTileK : kTileR, at = ks ? tile : tile - total_k;
+    const ChainDev& d = ch[find_chain(ch, nch, at, cls)];
+    const int lt = at - d.tb[cls];
     const bool acc = what == C_HMC ? d.P[kAcc] != 0.0 : d.P[kRjAcc] != 0.0;
-    if (what == C_HMC && acc) continue;
-    if (what == C_RJ && !acc) continue;
+    if (!ks) {
+      if (!acc) continue;
+      const uint32_t nv4 = (uint32_t)(d.nv / 4), base4 = (uint32_t)lt * (kElemPerTile / 4);
+      for (uint32_t j = threadIdx.x; j < kElemPerTile / 4; j += kWideThreads) {
+        const uint32_t i4 = base4 + j;
+        if (i4 >= nv4) break;
+        gst4(d.dr, i4, gld4(d.drn, i4));
+      }
+      continue;
+    }
+    if (acc == (what == C_HMC)) continue;
     const uint32_t nh2 = (uint32_t)(d.nh / 2), base2 = (uint32_t)lt * (kElemPerTile / 2);
     float* dk = (float*)d.dk;
     float* gk = (float*)d.gk;
@@ -2439,21 +2456,6 @@ __global__ void __launch_bounds__(kWideThreads) k_commit_k(const ChainDev* __res
     }
   }
 }
-__global__ void __launch_bounds__(kWideThreads) k_commit_r(const ChainDev* __restrict__ ch,
-                                                            int nch, int total, int what) {
-  for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
-    const ChainDev& d = ch[find_chain(ch, nch, tile, kTileR)];
-    const int lt = tile - d.tb[kTileR];
-    const bool acc = what == C_HMC ? d.P[kAcc] != 0.0 : d.P[kRjAcc] != 0.0;
-    if (!acc) continue;
-    const uint32_t nv4 = (uint32_t)(d.nv / 4), base4 = (uint32_t)lt * (kElemPerTile / 4);
-    for (uint32_t j = threadIdx.x; j < kElemPerTile / 4; j += kWideThreads) {
-      const uint32_t i4 = base4 + j;
-      if (i4 >= nv4) break;
-      gst4(d.dr, i4, gld4(d.drn, i4));
-    }
-  }
-}
 
 __global__ void __launch_bounds__(kThreads) k_copy_real(const ChainDev* __restrict__ ch,
                                                          int total, const float* src, float* dst) {
@@ -2470,12 +2472,14 @@ __device__ double tile_sum(const double* p, int n, double* red) {
   return block_sum(acc, red);
 }
 
+// block (i, chain): slot + i into P[dst + i]
 __global__ void __launch_bounds__(kThreads) k_reduce_slot(const ChainDev* __restrict__ ch,
                                                            int slot, int dst, int cls, int mean) {
   __shared__ double red[4];
-  const ChainDev& d = ch[blockIdx.x];
-  const double s = tile_sum(d.part + (size_t)slot * d.maxtiles, d.nt[cls], red);
-  if (threadIdx.x == 0) d.P[dst] = mean ? s / (double)d.nv : s;
+  const ChainDev& d = ch[blockIdx.y];
+  const int i = blockIdx.x;
+  const double s = tile_sum(d.part + (size_t)(slot + i) * d.maxtiles, d.nt[cls], red);
+  if (threadIdx.x == 0) d.P[dst + i] = mean ? s / (double)d.nv : s;
 }
 
 // Column sums of per-tile partials (src 0: shpart [shell][tile]; src 1: mpart
@@ -2508,21 +2512,30 @@ __global__ void __launch_bounds__(kThreads) k_colsum(const ChainDev* __restrict_
 }
 
 // shell tables from lambda and mean(alpha): 1/lambda, 1/m, sqrt(m), m = 1/lambda + abar
+__device__ __forceinline__ void shell_tables(const ChainDev& d, int m, double lam, double abar) {
+  const double il = 1.0 / lam;
+  // plain mass m_k = 1/lambda + mean(alpha); the real-space diagonal variant
+  // M^-1 = P diag(v) P takes m_k = 1/mean(v) for every mode (with D = v/mean(v))
+  const double ms = d.mass_flat ? 1.0 / d.P[kLmean] : il + abar;
+  d.td[kDInvLam + m] = il;
+  d.td[kDInvMass + m] = 1.0 / ms;
+  d.tf[kTInvLam + m] = (float)il;
+  d.tf[kTInvMass + m] = (float)(1.0 / ms);
+  d.tf[kTSqrtMass + m] = (float)sqrt(ms);
+  d.tf[kTScale + m] = 1.f;
+}
 __global__ void k_tables(const ChainDev* __restrict__ ch) {
   const ChainDev& d = ch[blockIdx.x];
-  const double abar = d.P[kAbar];
-  for (int m = threadIdx.x; m < d.nb; m += blockDim.x) {
-    const double il = 1.0 / d.P[kLam + m];
-    // plain mass m_k = 1/lambda + mean(alpha); the real-space diagonal variant
-    // M^-1 = P diag(v) P takes m_k = 1/mean(v) for every mode (with D = v/mean(v))
-    const double ms = d.mass_flat ? 1.0 / d.P[kLmean] : il + abar;
-    d.td[kDInvLam + m] = il;
-    d.td[kDInvMass + m] = 1.0 / ms;
-    d.tf[kTInvLam + m] = (float)il;
-    d.tf[kTInvMass + m] = (float)(1.0 / ms);
-    d.tf[kTSqrtMass + m] = (float)sqrt(ms);
-    d.tf[kTScale + m] = 1.f;
-  }
+  for (int m = threadIdx.x; m < d.nb; m += blockDim.x) shell_tables(d, m, d.P[kLam + m], d.P[kAbar]);
+}
+// mean(alpha) from the tiles' sums, then the tables
+__global__ void __launch_bounds__(kThreads) k_alpha_tables(const ChainDev* __restrict__ ch) {
+  __shared__ double red[4];
+  const ChainDev& d = ch[blockIdx.x];
+  const double abar =
+      tile_sum(d.part + (size_t)kPartAlpha * d.maxtiles, d.nt[kTileR], red) / (double)d.nv;
+  if (threadIdx.x == 0) d.P[kAbar] = abar;
+  for (int m = threadIdx.x; m < d.nb; m += kThreads) shell_tables(d, m, d.P[kLam + m], abar);
 }
 
 // Metropolis test of eq. acceptance_rule: accept iff ln u < -dH (u: Philox stream 4)
@@ -2542,51 +2555,76 @@ __device__ __forceinline__ bool accept_chain(const ChainDev& d, double K0, doubl
   if (acc) d.P[kDcur] = D1;
   return acc;
 }
-__global__ void k_accept(const ChainDev* __restrict__ ch) {
+// the proposal's energies from the tiles' sums, then the test
+__global__ void __launch_bounds__(kThreads) k_accept(const ChainDev* __restrict__ ch) {
+  __shared__ double red[4];
   const ChainDev& d = ch[blockIdx.x];
+  const double K1 = tile_sum(d.part + (size_t)kPartKin * d.maxtiles, d.nt[kTileXY], red);
+  const double Pi1 = tile_sum(d.part + (size_t)kPartPri * d.maxtiles, d.nt[kTileXY], red);
+  const double D1 = tile_sum(d.part + (size_t)kPartDat * d.maxtiles, d.nt[kTileZ], red);
   if (threadIdx.x != 0) return;
-  accept_chain(d, d.P[kK0], d.P[kPi0], d.P[kK1], d.P[kPi1], d.P[kD1]);
+  d.P[kK1] = K1;
+  d.P[kPi1] = Pi1;
+  d.P[kD1] = D1;
+  accept_chain(d, d.P[kK0], d.P[kPi0], K1, Pi1, D1);
 }
 
-// P_m | delta: lambda_m = sigma_m / x_m, x_m ~ chi^2(n_m + 2 alpha - 2) = 2 Gamma(.)
-__global__ void k_draw_power(const ChainDev* __restrict__ ch) {
-  const ChainDev& d = ch[blockIdx.x];
-  const uint32_t sweep = *d.draw;
-  for (int m = threadIdx.x; m < d.nb; m += blockDim.x) {
-    const double nm = d.P[kNmodes + m];
-    // an empty shell or a field with no power in it leaves P_m unchanged
-    if (nm <= 0.0 || !(d.P[kSigma + m] > 0.0)) continue;
+// P_m | delta: lambda_m = sigma_m / x_m, x_m ~ chi^2(n_m + 2 alpha - 2) = 2 Gamma(.), with
+// sigma_m from the tiles' sums and the shell's tables after it: one block per (shell, chain)
+__global__ void __launch_bounds__(kThreads) k_draw_power(const ChainDev* __restrict__ ch) {
+  __shared__ double red[4];
+  const ChainDev& d = ch[blockIdx.y];
+  const int m = blockIdx.x;
+  if (m >= d.nb) return;
+  const double sigma = column_sum(d.shpart + (size_t)m * d.maxtiles, 1, d.nt[kTileK], red);
+  if (threadIdx.x != 0) return;
+  d.P[kSigma + m] = sigma;
+  const double nm = d.P[kNmodes + m];
+  double lam = d.P[kLam + m];
+  // an empty shell or a field with no power in it leaves P_m unchanged
+  if (nm > 0.0 && sigma > 0.0) {
     const double beta = nm + 2.0 * d.alpha_prior - 2.0;
-    const double g = hmcsamp::gamma_mt(0.5 * beta, d.seed, d.chain, sweep, (uint32_t)m);
+    const double g = hmcsamp::gamma_mt(0.5 * beta, d.seed, d.chain, *d.draw, (uint32_t)m);
     if (g > 0.0)
-      d.P[kLam + m] = d.P[kSigma + m] / (2.0 * g);
+      d.P[kLam + m] = lam = sigma / (2.0 * g);
     else
       d.P[kStatus] = 2.0;
   }
+  shell_tables(d, m, lam, d.P[kAbar]);
 }
 
-// Nbar^l ~ GIG(1 - N_obs/2, A, B), then b^l ~ N(D/C, 1/C) with the new Nbar^l
-__global__ void k_draw_nbar_bias(const ChainDev* __restrict__ ch) {
-  const ChainDev& d = ch[blockIdx.x];
+// Nbar^l ~ GIG(1 - N_obs/2, A, B), then b^l ~ N(D/C, 1/C) with the new Nbar^l: one block per
+// (subsample, chain), which sums the tiles' moments first; the draw is one wave's
+__global__ void __launch_bounds__(kThreads) k_draw_nbar_bias(const ChainDev* __restrict__ ch) {
+  __shared__ double red[4];
+  const ChainDev& d = ch[blockIdx.y];
+  const int l = blockIdx.x;
+  if (l >= d.nsub) return;
+  const size_t width = 3 * (size_t)d.nsub;
+  const double S1 = column_sum(d.mpart + 3 * l, width, d.nt[kTileR], red);
+  const double S2 = column_sum(d.mpart + 3 * l + 1, width, d.nt[kTileR], red);
+  const double Ts = column_sum(d.mpart + 3 * l + 2, width, d.nt[kTileR], red);
+  if (threadIdx.x >= 64) return;
   const uint32_t sweep = *d.draw;
-  for (int l = threadIdx.x; l < d.nsub; l += blockDim.x) {
-    const double b = d.P[kBias + l];
-    const double S0 = d.P[kS0 + l], Bs = d.P[kBsum + l], nobs = d.P[kNobs + l];
-    const double S1 = d.P[kS1 + l], S2 = d.P[kS2 + l], Ts = d.P[kTsum + l];
-    const double A = S0 + 2.0 * b * S1 + b * b * S2;
-    const double nb = hmcsamp::gig(1.0 - 0.5 * nobs, A, Bs, d.seed, d.chain, sweep, (uint32_t)l);
-    if (nb > 0.0)
-      d.P[kNbar + l] = nb;
-    else
-      d.P[kStatus] = 3.0;
-    if (!((d.fixed_mask >> l) & 1u) && S2 > 0.0) {  // S2 = 0: degenerate, b kept
-      const double nbl = d.P[kNbar + l];
-      const double C = nbl * S2, D = Ts - nbl * S1;
-      const hmcrng::U4 w = hmcrng::block(d.seed, d.chain, hmcrng::kBias, sweep, (uint32_t)l, 0);
-      double z, unused;
-      hmcrng::box_muller(w.w[0], w.w[1], &z, &unused);
-      d.P[kBias + l] = D / C + z / sqrt(C);
-    }
+  const double b = d.P[kBias + l], old = d.P[kNbar + l];
+  const double S0 = d.P[kS0 + l], Bs = d.P[kBsum + l], nobs = d.P[kNobs + l];
+  const double A = S0 + 2.0 * b * S1 + b * b * S2;
+  const double nb = hmcsamp::gig(1.0 - 0.5 * nobs, A, Bs, d.seed, d.chain, sweep, (uint32_t)l);
+  if (threadIdx.x != 0) return;
+  d.P[kS1 + l] = S1;
+  d.P[kS2 + l] = S2;
+  d.P[kTsum + l] = Ts;
+  if (nb > 0.0)
+    d.P[kNbar + l] = nb;
+  else
+    d.P[kStatus] = 3.0;
+  if (!((d.fixed_mask >> l) & 1u) && S2 > 0.0) {  // S2 = 0: degenerate, b kept
+    const double nbl = nb > 0.0 ? nb : old;
+    const double C = nbl * S2, D = Ts - nbl * S1;
+    const hmcrng::U4 w = hmcrng::block(d.seed, d.chain, hmcrng::kBias, sweep, (uint32_t)l, 0);
+    double z, unused;
+    hmcrng::box_muller(w.w[0], w.w[1], &z, &unused);
+    d.P[kBias + l] = D / C + z / sqrt(C);
   }
 }
 
@@ -2595,7 +2633,7 @@ __global__ void k_draw_nbar_bias(const ChainDev* __restrict__ ch) {
 // of the walls (the lambda the chain started from), never the current theta: the
 // move must run the same leapfrog map from either end for detailed balance.
 // BEGIN: theta0, mass, momenta (stream 8), H0, first half kick and drift.
-// STEP:  kick with dU at the current theta, drift.
+// STEP (k_rj_step): kick with dU at the current theta, drift.
 // END:   last half kick, H1, Metropolis test (stream 9), lambda update.
 // dU_m = 1/2 sum_{k in m} w Re(conj(delta_hat) g_hat) + (alpha - 1) from the tile partials.
 // Mirror th into [lo, hi], negating rho once per reflection; returns the count.
@@ -2629,6 +2667,27 @@ __device__ __forceinline__ bool rj_accept(const ChainDev& d, double k1, double s
   d.P[kRjAcc] = acc ? 1.0 : 0.0;
   if (acc) d.P[kDcur] = D1;
   return acc;
+}
+
+// RJ_STEP: a shell's step needs only its own dU, so the block that sums the tiles' shell dots
+// of a shell also steps it: one block per (shell, chain), one launch a step where the
+// column sums and the phase kernel were two (256^3: 5.1 + 4.6 -> 6.1 us)
+__global__ void __launch_bounds__(kThreads) k_rj_step(const ChainDev* __restrict__ ch) {
+  __shared__ double red[4];
+  const ChainDev& d = ch[blockIdx.y];
+  const int m = blockIdx.x;
+  if (m >= d.nb) return;
+  const double s = column_sum(d.shpart + (size_t)m * d.maxtiles, 1, d.nt[kTileXY], red);
+  if (threadIdx.x != 0) return;
+  const double dU = 0.5 * s + (d.alpha_prior - 1.0), eps = d.eps;
+  double th = d.P[kTheta + m], rho = d.P[kRho + m];
+  const double ms = d.P[kMth + m];
+  rho -= eps * dU;
+  th += eps * rho / ms;
+  d.P[kWall + m] += (double)rj_reflect(&th, &rho, d.P[kLo + m], d.P[kHi + m]);
+  d.P[kTheta + m] = th;
+  d.P[kRho + m] = rho;
+  d.tf[kTScale + m] = (float)exp(0.5 * (th - d.P[kTheta0 + m]));
 }
 
 __global__ void __launch_bounds__(kThreads) k_rj(const ChainDev* __restrict__ ch, int phase) {
@@ -2671,18 +2730,8 @@ __global__ void __launch_bounds__(kThreads) k_rj(const ChainDev* __restrict__ ch
       d.P[kRho + m] = rho;
       d.tf[kTScale + m] = (float)exp(0.5 * (th - d.P[kTheta0 + m]));
     }
-  } else if (phase == RJ_STEP) {
-    if (on) {
-      double th = d.P[kTheta + m], rho = d.P[kRho + m];
-      const double ms = d.P[kMth + m];
-      rho -= eps * dU;
-      th += eps * rho / ms;
-      d.P[kWall + m] += (double)rj_reflect(&th, &rho, d.P[kLo + m], d.P[kHi + m]);
-      d.P[kTheta + m] = th;
-      d.P[kRho + m] = rho;
-      d.tf[kTScale + m] = (float)exp(0.5 * (th - d.P[kTheta0 + m]));
-    }
   } else {
+    const double D1 = tile_sum(d.part + (size_t)kPartDat * d.maxtiles, d.nt[kTileZ], red);
     double th = 0.0, rho = 0.0, ms = 1.0;
     if (on) {
       th = d.P[kTheta + m];
@@ -2693,7 +2742,10 @@ __global__ void __launch_bounds__(kThreads) k_rj(const ChainDev* __restrict__ ch
     const double st = block_sum(on ? th : 0.0, red);
     const double hits = block_sum(on ? d.P[kWall + m] : 0.0, red);
     __shared__ int acc_s;
-    if (m == 0) acc_s = rj_accept(d, k1, st, hits, d.P[kD1]);
+    if (m == 0) {
+      d.P[kD1] = D1;
+      acc_s = rj_accept(d, k1, st, hits, D1);
+    }
     __syncthreads();
     if (on && acc_s) d.P[kLam + m] = exp(th);
   }
@@ -3244,10 +3296,8 @@ void launch_shell_index(const ChainDev* ch, int total, int16_t* out, hipStream_t
 }
 void launch_commit(int what, const ChainDev* ch, int nch, int total_k, int total_r,
                    hipStream_t s) {
-  hipLaunchKernelGGL(k_commit_k, dim3(eg(total_k)), dim3(kWideThreads), 0, s, ch, nch, total_k,
-                     what);
-  hipLaunchKernelGGL(k_commit_r, dim3(eg(total_r)), dim3(kWideThreads), 0, s, ch, nch, total_r,
-                     what);
+  const int total = total_k + total_r;
+  hipLaunchKernelGGL(k_commit, dim3(eg(total)), dim3(kWideThreads), 0, s, ch, nch, total_k, total, what);
 }
 void launch_copy_real(const ChainDev* ch, int total_r, const float* src, float* dst,
                       hipStream_t s) {
@@ -3255,8 +3305,8 @@ void launch_copy_real(const ChainDev* ch, int total_r, const float* src, float* 
                      dst);
 }
 void launch_reduce_slot(const ChainDev* ch, int nch, int slot, int dst, int cls, hipStream_t s,
-                        bool mean) {
-  hipLaunchKernelGGL(k_reduce_slot, dim3(nch), dim3(kThreads), 0, s, ch, slot, dst, cls,
+                        bool mean, int count) {
+  hipLaunchKernelGGL(k_reduce_slot, dim3(count, nch), dim3(kThreads), 0, s, ch, slot, dst, cls,
                      mean ? 1 : 0);
 }
 void launch_colsum(const ChainDev* ch, int nch, int width, int src, int cls, int dst, int mode,
@@ -3272,16 +3322,23 @@ __global__ void k_set_draw(uint32_t* p, uint32_t v) {
 void launch_set_draw(uint32_t* p, uint32_t v, hipStream_t s) {
   hipLaunchKernelGGL(k_set_draw, dim3(1), dim3(64), 0, s, p, v);
 }
+void launch_alpha_tables(const ChainDev* ch, int nch, hipStream_t s) {
+  hipLaunchKernelGGL(k_alpha_tables, dim3(nch), dim3(kThreads), 0, s, ch);
+}
 void launch_accept(const ChainDev* ch, int nch, hipStream_t s) {
-  hipLaunchKernelGGL(k_accept, dim3(nch), dim3(64), 0, s, ch);
+  hipLaunchKernelGGL(k_accept, dim3(nch), dim3(kThreads), 0, s, ch);
 }
-void launch_draw_power(const ChainDev* ch, int nch, hipStream_t s) {
-  hipLaunchKernelGGL(k_draw_power, dim3(nch), dim3(kMaxBins), 0, s, ch);
+void launch_draw_power(const ChainDev* ch, int nch, int nb_max, hipStream_t s) {
+  hipLaunchKernelGGL(k_draw_power, dim3(nb_max, nch), dim3(kThreads), 0, s, ch);
 }
-void launch_draw_nbar_bias(const ChainDev* ch, int nch, hipStream_t s) {
-  hipLaunchKernelGGL(k_draw_nbar_bias, dim3(nch), dim3(64), 0, s, ch);
+void launch_draw_nbar_bias(const ChainDev* ch, int nch, int sub_max, hipStream_t s) {
+  hipLaunchKernelGGL(k_draw_nbar_bias, dim3(sub_max, nch), dim3(kThreads), 0, s, ch);
 }
 void launch_rj(int phase, const ChainDev* ch, int nch, int nb_max, hipStream_t s, int cls) {
+  if (phase == RJ_STEP) {
+    hipLaunchKernelGGL(k_rj_step, dim3(nb_max, nch), dim3(kThreads), 0, s, ch);
+    return;
+  }
   launch_colsum(ch, nch, nb_max, 0, cls, kDU, 2, s);  // dU from the per-tile shell dots
   hipLaunchKernelGGL(k_rj, dim3(nch), dim3(kThreads), 0, s, ch, phase);
 }

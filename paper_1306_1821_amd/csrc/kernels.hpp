@@ -108,19 +108,22 @@ void launch_commit(int what, const ChainDev* ch, int nch, int total_k, int total
 void launch_copy_real(const ChainDev* ch, int total_r, const float* src, float* dst,
                       hipStream_t s);
 
-// per-chain scalar kernels (one block per chain)
+// per-chain scalar kernels
+// tile sums of slots slot .. slot + count - 1 into P[dst ..]
 void launch_reduce_slot(const ChainDev* ch, int nch, int slot, int dst, int cls, hipStream_t s,
-                        bool mean = false);
+                        bool mean = false, int count = 1);
 // column sums of tile partials; src 0 shpart / 1 mpart; mode: see kernels.hip
 void launch_colsum(const ChainDev* ch, int nch, int width, int src, int cls, int dst, int mode,
                    hipStream_t s);
 void launch_tables(const ChainDev* ch, int nch, hipStream_t s);
+void launch_alpha_tables(const ChainDev* ch, int nch, hipStream_t s);  // mean(alpha), then the tables
 // the Philox draw index (trajectory or sweep) lives in device memory so that a
 // captured graph can be replayed for any index
 void launch_set_draw(uint32_t* p, uint32_t v, hipStream_t s);
+// the draws and the tests sum the tiles' partials themselves
 void launch_accept(const ChainDev* ch, int nch, hipStream_t s);
-void launch_draw_power(const ChainDev* ch, int nch, hipStream_t s);
-void launch_draw_nbar_bias(const ChainDev* ch, int nch, hipStream_t s);
+void launch_draw_power(const ChainDev* ch, int nch, int nb_max, hipStream_t s);  // and the tables
+void launch_draw_nbar_bias(const ChainDev* ch, int nch, int sub_max, hipStream_t s);
 void launch_rj(int phase, const ChainDev* ch, int nch, int nb_max, hipStream_t s,
                int cls = kTileXY);
 

@@ -363,8 +363,7 @@ static hmc_status pull_params(hmc_ctx* c) {
 static hmc_status refresh_coefficients(hmc_ctx* c) {
   const int nch = (int)c->ch.size();
   launch_coeff(c->d_all, nch, c->total[kTileR], c->stream);
-  launch_reduce_slot(c->d_all, nch, kPartAlpha, kAbar, kTileR, c->stream, true);
-  launch_tables(c->d_all, nch, c->stream);
+  launch_alpha_tables(c->d_all, nch, c->stream);
   return check_launch(c);
 }
 
@@ -697,8 +696,7 @@ static hmc_status run_trajectory_learned(hmc_ctx* c) {
   q.z(Z_NOISE, 0);
   q.y(+1);
   q.xl(L_START, 0.f, 0.f);
-  launch_reduce_slot(c->d_all, nch, kPartKin, kK0, kTileXY, c->stream);
-  launch_reduce_slot(c->d_all, nch, kPartPri, kPi0, kTileXY, c->stream);
+  launch_reduce_slot(c->d_all, nch, kPartKin, kK0, kTileXY, c->stream, false, 2);  // K0, Pi0
   force(0);
   q.xl(L_KICK, 0.5f, 0.f, kflags);
   for (int s = 1; s <= c->cur_steps; ++s) {
@@ -714,9 +712,6 @@ static hmc_status run_trajectory_learned(hmc_ctx* c) {
     force(last ? (ZF_WRITE_DRN | ZF_DATA) : 0);
     q.xl(last ? L_KICK_LAST : L_KICK, last ? 0.5f : 1.f, 0.f, kflags);
   }
-  launch_reduce_slot(c->d_all, nch, kPartKin, kK1, kTileXY, c->stream);
-  launch_reduce_slot(c->d_all, nch, kPartPri, kPi1, kTileXY, c->stream);
-  launch_reduce_slot(c->d_all, nch, kPartDat, kD1, kTileZ, c->stream);
   launch_accept(c->d_all, nch, c->stream);
   launch_commit(C_HMC, c->d_all, nch, c->total[kTileK], c->total[kTileR], c->stream);
   return refresh_gradient(c, false);
@@ -739,17 +734,13 @@ static hmc_status run_trajectory(hmc_ctx* c) {
   q.z(Z_NOISE, 0);
   q.y(+1);
   q.x(X_START, 0.5f, 1.f, 0);
-  launch_reduce_slot(c->d_all, nch, kPartKin, kK0, kTileXY, c->stream);
-  launch_reduce_slot(c->d_all, nch, kPartPri, kPi0, kTileXY, c->stream);
+  launch_reduce_slot(c->d_all, nch, kPartKin, kK0, kTileXY, c->stream, false, 2);  // K0, Pi0
   for (int s = 1; s < c->cur_steps; ++s) {
     q.yz(0);
     q.x(X_STEP, 1.f, 1.f, 0);
   }
   q.yz(ZF_WRITE_DRN | ZF_DATA);
   q.x(X_END, 0.5f, 0.f, 0);
-  launch_reduce_slot(c->d_all, nch, kPartKin, kK1, kTileXY, c->stream);
-  launch_reduce_slot(c->d_all, nch, kPartPri, kPi1, kTileXY, c->stream);
-  launch_reduce_slot(c->d_all, nch, kPartDat, kD1, kTileZ, c->stream);
   launch_accept(c->d_all, nch, c->stream);
   launch_commit(C_HMC, c->d_all, nch, c->total[kTileK], c->total[kTileR], c->stream);
   return check_launch(c);
@@ -829,9 +820,7 @@ static hmc_status run_sweep(hmc_ctx* c) {
   if (st != HMC_OK) return st;
   // P | delta
   launch_shell_power(c->d_all, nch, c->total[kTileK], c->stream);
-  launch_colsum(c->d_all, nch, c->max_nb, 0, kTileK, kSigma, 0, c->stream);
-  launch_draw_power(c->d_all, nch, c->stream);
-  launch_tables(c->d_all, nch, c->stream);
+  launch_draw_power(c->d_all, nch, c->max_nb, c->stream);
   // joint (P, delta) move for chains that ask for it (all or none in a batch)
   bool any_rj = false;
   for (auto& k : c->ch) any_rj |= k.cfg.rj_move != 0;
@@ -852,7 +841,6 @@ static hmc_status run_sweep(hmc_ctx* c) {
       if (!last) {
         launch_rj(RJ_STEP, c->d_all, nch, c->max_nb, c->stream);
       } else {
-        launch_reduce_slot(c->d_all, nch, kPartDat, kD1, kTileZ, c->stream);
         launch_rj(RJ_END, c->d_all, nch, c->max_nb, c->stream);
       }
     }
@@ -862,8 +850,7 @@ static hmc_status run_sweep(hmc_ctx* c) {
   }
   // Nbar | delta, b and b | delta, Nbar
   launch_moments(c->d_all, nch, c->total[kTileR], c->stream);
-  launch_colsum(c->d_all, nch, 3 * c->max_sub, 1, kTileR, kS1, 1, c->stream);
-  launch_draw_nbar_bias(c->d_all, nch, c->stream);
+  launch_draw_nbar_bias(c->d_all, nch, c->max_sub, c->stream);
   // alpha, beta, mass and gradient for the new parameters
   if ((st = refresh_coefficients(c)) != HMC_OK) return st;
   return refresh_gradient(c, false);
@@ -1013,8 +1000,7 @@ hmc_status hmc_set_coefficients(hmc_ctx* c, int32_t chain, const float* alpha_de
   // mean(alpha) from the new field: reuse the coefficient partial slot via the
   // real-space energy kernel layout (sum of alpha per tile)
   launch_alpha_sum(k.solo, 1, k.dev.nt[kTileR], c->stream);
-  launch_reduce_slot(k.solo, 1, kPartAlpha, kAbar, kTileR, c->stream, true);
-  launch_tables(k.solo, 1, c->stream);
+  launch_alpha_tables(k.solo, 1, c->stream);
   return refresh_gradient(c, true);
 }
 

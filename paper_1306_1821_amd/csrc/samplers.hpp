@@ -1,4 +1,4 @@
-// Scalar float64 samplers for the Gibbs blocks, one thread per draw.
+// Scalar float64 samplers for the Gibbs blocks, one thread per draw (GIG: one wave).
 //
 // chi^2_beta = 2 Gamma(beta/2): Marsaglia & Tsang (2000), attempt j on Philox
 //   block j (words 0,1 -> normal by Box-Muller cosine branch, word 2 -> the
@@ -64,26 +64,47 @@ __device__ inline double gig_bisect(const GigBox& b, double lo, double hi) {
   return 0.5 * (lo + hi);
 }
 
-__device__ inline GigBox gig_box(double lam, double om) {
+// The two bisections of a wave at once: lanes 0-31 take the root above m, lanes 32-63 the one
+// below.  Each half evaluates 32 interior points of its bracket per round and keeps the
+// interval in which the (decreasing) F changes sign, so a round gains 5 bits where a bisection
+// step gains one: 53 + 53 dependent steps of three divisions each were most of the draw
+// (23 us); the last bits are gig_bisect's.  Every lane returns its half's root.
+__device__ inline double gig_roots_wave(const GigBox& b, double lo, double hi) {
+  const int lane = threadIdx.x & 63, k = lane & 31;
+  for (int i = 0; i < 10; ++i) {
+    const double w = (hi - lo) * (1.0 / 33.0);
+    const unsigned long long pos = __ballot(gig_F(b, lo + w * (double)(k + 1)) > 0.0);
+    const int n = __popc((unsigned)(lane < 32 ? pos : pos >> 32));  // points before the sign change
+    if (w > 4e-15 * hi) {  // the points are distinct; the last few hundred ulps are bisected
+      if (n < 32) hi = lo + w * (double)(n + 1);
+      if (n > 0) lo = lo + w * (double)n;
+    }
+  }
+  return gig_bisect(b, lo, hi);
+}
+
+// vm, vp of the whole wave's box (every lane of the wave calls this)
+__device__ inline GigBox gig_box_wave(double lam, double om) {
   GigBox b;
   b.lam = lam;
   b.om = om;
   b.m = ((lam - 1.0) + sqrt((lam - 1.0) * (lam - 1.0) + om * om)) / om;
   double step = b.m;
   for (int i = 0; i < 2000 && gig_F(b, b.m + step) > 0.0; ++i) step *= 2.0;
-  const double zp = gig_bisect(b, b.m, b.m + step);
-  double lo = 0.5 * b.m;
-  for (int i = 0; i < 2000 && gig_F(b, lo) < 0.0; ++i) lo *= 0.5;
-  const double zm = gig_bisect(b, lo, b.m);
-  b.vp = (zp - b.m) * exp(0.5 * gig_lh(b, zp));
-  b.vm = (zm - b.m) * exp(0.5 * gig_lh(b, zm));
+  double below = 0.5 * b.m;
+  for (int i = 0; i < 2000 && gig_F(b, below) < 0.0; ++i) below *= 0.5;
+  const bool up = (threadIdx.x & 63) < 32;
+  const double z = gig_roots_wave(b, up ? b.m : below, up ? b.m + step : b.m);
+  const double v = (z - b.m) * exp(0.5 * gig_lh(b, z));
+  b.vp = __shfl(v, 0);
+  b.vm = __shfl(v, 32);
   return b;
 }
 
-// Returns a GIG(p, A, B) variate, or -1 if no attempt was accepted.
+// Returns a GIG(p, A, B) variate, or -1 if no attempt was accepted (the whole wave calls this).
 __device__ inline double gig(double p, double A, double B, uint64_t seed, uint32_t chain,
                              uint32_t draw, uint32_t sub) {
-  const GigBox b = gig_box(fabs(p), sqrt(A * B));
+  const GigBox b = gig_box_wave(fabs(p), sqrt(A * B));
   for (int j = 0; j < kMaxAttempts; ++j) {
     hmcrng::U4 w = hmcrng::block(seed, chain, hmcrng::kGig, draw, sub, (uint32_t)j);
     const double u = hmcrng::uniform(w.w[0]);
