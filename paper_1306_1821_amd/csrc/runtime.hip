@@ -98,7 +98,8 @@ struct hmc_ctx {
   hipStream_t stream = nullptr;
   ChainDev* d_all = nullptr;
   float2* tw = nullptr;
-  double* pinned = nullptr;  // staging for host results
+  double* P_all = nullptr;   // every chain's parameter block, back to back
+  double* pinned = nullptr;  // the same on the host, for one copy of all results
   int total[kTileClasses] = {0, 0, 0, 0};
   int lds_x = 0, lds_z = 0;
   int grid[3] = {0, 0, 0};  // launch grid per pass class (x, y, z); 0: one workgroup per tile
@@ -352,10 +353,13 @@ static hmc_status push_params(hmc_ctx* c, Chain& k) {
   return HMC_OK;
 }
 static hmc_status pull_params(hmc_ctx* c) {
-  for (auto& k : c->ch)
-    HIPCHK(c, hipMemcpyAsync(k.hp.data(), k.dev.P, kPSize * sizeof(double),
-                             hipMemcpyDeviceToHost, c->stream));
+  // one copy into pinned memory (a copy per chain into pageable memory is staged and
+  // waited for one by one: a trajectory of eight 64^3 chains 945 -> 848 us)
+  HIPCHK(c, hipMemcpyAsync(c->pinned, c->P_all, c->ch.size() * kPSize * sizeof(double),
+                           hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
+  for (size_t i = 0; i < c->ch.size(); ++i)
+    memcpy(c->ch[i].hp.data(), c->pinned + i * kPSize, kPSize * sizeof(double));
   return HMC_OK;
 }
 
@@ -447,7 +451,6 @@ void hmc_destroy(hmc_ctx* ctx) {
   if (ctx->gstream) (void)hipStreamDestroy(ctx->gstream);
   if (ctx->d_draw) (void)hipFree(ctx->d_draw);
   for (auto& k : ctx->ch) {
-    (void)hipFree(k.dev.P);
     (void)hipFree(k.dev.tf);
     (void)hipFree(k.dev.td);
     (void)hipFree(k.solo);
@@ -455,6 +458,7 @@ void hmc_destroy(hmc_ctx* ctx) {
   (void)hipFree(ctx->d_all);
   for (auto& g : ctx->groups) (void)hipFree(g.d);
   (void)hipFree(ctx->tw);
+  (void)hipFree(ctx->P_all);
   if (ctx->pinned) (void)hipHostFree(ctx->pinned);
   delete ctx;
 }
@@ -514,8 +518,10 @@ hmc_status hmc_init_batch(const hmc_config* cfg, const hmc_buffers* buf, int32_t
     c->err = "hipMalloc draw counter";
     return bail(HMC_EDEVICE);
   }
-  if (hipHostMalloc((void**)&c->pinned, 64 * sizeof(double), 0) != hipSuccess) {
-    c->err = "hipHostMalloc";
+  const size_t pbytes = (size_t)n_chains * kPSize * sizeof(double);
+  if (hipMalloc(&c->P_all, pbytes) != hipSuccess ||
+      hipHostMalloc((void**)&c->pinned, pbytes, 0) != hipSuccess) {
+    c->err = "hipMalloc parameter blocks";
     return bail(HMC_EDEVICE);
   }
   int boff = 0, soff = 0;
@@ -571,11 +577,11 @@ hmc_status hmc_init_batch(const hmc_config* cfg, const hmc_buffers* buf, int32_t
     d.smass = (float*)(w + L.smass);
     d.lut = (signed char*)(w + L.lut);
     d.obs = (unsigned long long*)(w + L.obs);
-    if (hipMalloc(&d.P, kPSize * sizeof(double)) != hipSuccess ||
-        hipMalloc(&d.tf, kTSize * sizeof(float)) != hipSuccess ||
+    d.P = c->P_all + (size_t)i * kPSize;
+    if (hipMalloc(&d.tf, kTSize * sizeof(float)) != hipSuccess ||
         hipMalloc(&d.td, kDSize * sizeof(double)) != hipSuccess ||
         hipMalloc(&k.solo, sizeof(ChainDev)) != hipSuccess) {
-      c->err = "hipMalloc parameter block";
+      c->err = "hipMalloc shell tables";
       return bail(HMC_EDEVICE);
     }
     k.hp.assign(kPSize, 0.0);
