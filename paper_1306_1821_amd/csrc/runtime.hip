@@ -9,6 +9,7 @@
 
 #include <algorithm>
 #include <map>
+#include <mutex>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -26,6 +27,39 @@ namespace {
 
 thread_local std::string g_err = "";
 
+// Side streams of closed contexts, kept for the next one (creating a stream takes
+// milliseconds): at most kSpareStreams in the process, each owned by one context at a time and
+// idle when it comes back.
+constexpr size_t kSpareStreams = 8;
+std::mutex g_spare_mu;
+std::vector<std::pair<int, hipStream_t>> g_spare;  // device, stream
+
+hipError_t take_stream(hipStream_t* st) {
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  {
+    std::lock_guard<std::mutex> lock(g_spare_mu);
+    for (size_t i = 0; i < g_spare.size(); ++i)
+      if (g_spare[i].first == dev) {
+        *st = g_spare[i].second;
+        g_spare.erase(g_spare.begin() + i);
+        return hipSuccess;
+      }
+  }
+  return hipStreamCreateWithFlags(st, hipStreamNonBlocking);
+}
+void give_stream(int dev, hipStream_t st) {
+  if (hipStreamSynchronize(st) == hipSuccess) {
+    std::lock_guard<std::mutex> lock(g_spare_mu);
+    if (g_spare.size() < kSpareStreams) {
+      g_spare.emplace_back(dev, st);
+      return;
+    }
+  }
+  (void)hipStreamDestroy(st);
+}
+
 struct Chain {
   hmc_config cfg;
   hmc_buffers buf;
@@ -34,6 +68,9 @@ struct Chain {
   ChainDev* solo;        // device descriptor with tile bases at zero
   std::vector<double> hp;  // host mirror of the parameter block
 };
+
+// a context of one grid size runs in two parts from this many voxels on (see split)
+constexpr long long kSplitVoxels = 12000000;
 
 struct WsLayout {
   size_t T, bdk, bgk, drn, part, shpart, mpart, T2, T3, shat, smass, lut, obs, total;
@@ -117,6 +154,12 @@ struct hmc_ctx {
     ChainDev* d = nullptr;
   };
   std::vector<Group> groups;
+  // chains that advance on a stream of their own: the size groups of a batch, or the two
+  // halves of a single-size context (see split)
+  std::vector<Group> parts;
+  std::vector<hipStream_t> side;   // streams of parts 1, 2, ... (part 0: the caller's)
+  int dev = 0;                     // their device
+  std::vector<hipEvent_t> side_ev;  // [0] fork, [i] end of part i
   bool grouped[3] = {false, false, false};  // per pass class (x, y, z)
   int plan[3] = {0, 0, 0};  // radix plan per pass class for single-size launches
   bool plane_pass = true;   // fused y-z plane pass where the grid size has one
@@ -208,7 +251,8 @@ struct Seq {
   int nch;
   const int* tot;
   hipStream_t s;
-  int un;  // N shared by all chains, or 0
+  int un;      // N shared by all chains, or 0
+  bool batch;  // part of a batch of several sizes
   // calls f(descriptors, chains, tile totals, uniform N, grid) once for the whole
   // batch, or once per size group when the class runs grouped
   template <class F>
@@ -291,7 +335,9 @@ struct Seq {
     z(Z_GRAD, zflags);
     y(+1);
   }
-  bool planes() const { return c->plane_pass && un != 0 && plane_pass_supported(un); }
+  bool planes() const {
+    return c->plane_pass && un != 0 && (batch ? plane_pass_batches(un) : plane_pass_supported(un));
+  }
   void yzl(int kind, int zflags) {
     Timed tm(c, 3, s);
     launch_yzpass(d, nch, ZArgs{zflags, 0, nullptr}, c->tw, s, un, kind);
@@ -306,15 +352,21 @@ struct Seq {
 };
 
 Seq seq_all(hmc_ctx* c) {
-  return Seq{c, c->d_all, (int)c->ch.size(), c->total, c->stream, c->uniform_n};
+  return Seq{c, c->d_all, (int)c->ch.size(), c->total, c->stream, c->uniform_n, c->uniform_n == 0};
+}
+Seq seq_part(hmc_ctx* c, const hmc_ctx::Group& g, hipStream_t s) {
+  return Seq{c, g.d, g.nch, g.total, s, g.n, c->uniform_n == 0};
 }
 
 }  // namespace
 
+static void refresh_gradient(Seq& q, bool write_dr) {
+  q.gradient(ZF_DATA | (write_dr ? ZF_WRITE_DR : 0), 0);
+  launch_reduce_slot(q.d, q.nch, kPartDat, kDcur, kTileZ, q.s);
+}
 static hmc_status refresh_gradient(hmc_ctx* c, bool write_dr) {
   Seq q = seq_all(c);
-  q.gradient(ZF_DATA | (write_dr ? ZF_WRITE_DR : 0), 0);
-  launch_reduce_slot(c->d_all, (int)c->ch.size(), kPartDat, kDcur, kTileZ, c->stream);
+  refresh_gradient(q, write_dr);
   return check_launch(c);
 }
 
@@ -328,7 +380,11 @@ static hmc_status upload_desc(hmc_ctx* c) {
     for (int j = 0; j < kTileClasses; ++j) s.tb[j] = 0;
     HIPCHK(c, hipMemcpyAsync(k.solo, &s, sizeof(ChainDev), hipMemcpyHostToDevice, c->stream));
   }
-  for (auto& g : c->groups) {
+  std::vector<hmc_ctx::Group*> lists;
+  for (auto& g : c->groups) lists.push_back(&g);
+  for (auto& g : c->parts) lists.push_back(&g);
+  for (auto* gp : lists) {
+    auto& g = *gp;
     std::vector<ChainDev> gd;
     int base[kTileClasses] = {0, 0, 0, 0};
     for (int i : g.members) {
@@ -363,11 +419,14 @@ static hmc_status pull_params(hmc_ctx* c) {
   return HMC_OK;
 }
 
-// recompute alpha, beta, mean(alpha), shell tables for all chains
+// recompute alpha, beta, mean(alpha), shell tables
+static void refresh_coefficients(Seq& q) {
+  launch_coeff(q.d, q.nch, q.tot[kTileR], q.s);
+  launch_alpha_tables(q.d, q.nch, q.s);
+}
 static hmc_status refresh_coefficients(hmc_ctx* c) {
-  const int nch = (int)c->ch.size();
-  launch_coeff(c->d_all, nch, c->total[kTileR], c->stream);
-  launch_alpha_tables(c->d_all, nch, c->stream);
+  Seq q = seq_all(c);
+  refresh_coefficients(q);
   return check_launch(c);
 }
 
@@ -457,6 +516,9 @@ void hmc_destroy(hmc_ctx* ctx) {
   }
   (void)hipFree(ctx->d_all);
   for (auto& g : ctx->groups) (void)hipFree(g.d);
+  for (auto& g : ctx->parts) (void)hipFree(g.d);
+  for (auto st : ctx->side) give_stream(ctx->dev, st);
+  for (auto e : ctx->side_ev) (void)hipEventDestroy(e);
   (void)hipFree(ctx->tw);
   (void)hipFree(ctx->P_all);
   if (ctx->pinned) (void)hipHostFree(ctx->pinned);
@@ -636,6 +698,34 @@ hmc_status hmc_init_batch(const hmc_config* cfg, const hmc_buffers* buf, int32_t
         return bail(HMC_EDEVICE);
       }
   }
+  if (c->uniform_n == 0) {
+    c->parts = c->groups;
+    for (auto& g : c->parts) g.d = nullptr;
+  } else if (n_chains >= 2 && c->uniform_n >= 128 && n_chains * c->ch[0].dev.nv >= kSplitVoxels) {
+    c->parts.resize(2);
+    for (int i = 0; i < n_chains; ++i) {
+      auto& g = c->parts[2 * i < n_chains ? 0 : 1];
+      g.n = c->uniform_n;
+      g.nch += 1;
+      g.members.push_back(i);
+      for (int j = 0; j < kTileClasses; ++j) g.total[j] += c->ch[i].dev.nt[j];
+    }
+  }
+  for (size_t i = 0; i < c->parts.size(); ++i) {
+    hipEvent_t e = nullptr;
+    hipStream_t st = nullptr;
+    bool ok = hipMalloc(&c->parts[i].d, c->parts[i].nch * sizeof(ChainDev)) == hipSuccess &&
+              hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
+    if (e) c->side_ev.push_back(e);
+    if (ok && i > 0) {
+      ok = take_stream(&st) == hipSuccess && hipGetDevice(&c->dev) == hipSuccess;
+      if (st) c->side.push_back(st);
+    }
+    if (!ok) {
+      c->err = "part descriptors, events or streams";
+      return bail(HMC_EDEVICE);
+    }
+  }
   hmc_status st;
   for (auto& k : c->ch)
     if ((st = push_params(c, k)) != HMC_OK) return bail(st);
@@ -675,14 +765,10 @@ hmc_status hmc_init(const hmc_config* cfg, const hmc_buffers* buf, const double*
   return hmc_init_batch(cfg, buf, 1, bias, nbar, pk, stream, out);
 }
 
-// one density trajectory for every chain; results stay on the device
-// one density trajectory for every chain (draw index from the device counter);
-// no host synchronisation, so it can be captured in a graph
 // density trajectory with the learned mass (see the learned-mass passes in
 // kernels.hip); the plain gradient cache is refreshed after the Metropolis test
-static hmc_status run_trajectory_learned(hmc_ctx* c) {
-  Seq q = seq_all(c);
-  const int nch = (int)c->ch.size();
+static void trajectory_learned(Seq& q) {
+  hmc_ctx* const c = q.c;
   // the plane passes where the context has them (T, T2, T3 one round trip each), else the
   // separate y, z, y passes
   const bool planes = q.planes();
@@ -696,13 +782,13 @@ static hmc_status run_trajectory_learned(hmc_ctx* c) {
     q.y(-1, 0);
     q.y(-1, 2);
     q.zl(LZ_FORCE, zflags);
-    launch_reduce_slot(c->d_all, nch, kPartAux, kGbar, kTileZ, c->stream, true);
+    launch_reduce_slot(q.d, q.nch, kPartAux, kGbar, kTileZ, q.s, true);
     q.y(+1, 0);
   };
   q.z(Z_NOISE, 0);
   q.y(+1);
   q.xl(L_START, 0.f, 0.f);
-  launch_reduce_slot(c->d_all, nch, kPartKin, kK0, kTileXY, c->stream, false, 2);  // K0, Pi0
+  launch_reduce_slot(q.d, q.nch, kPartKin, kK0, kTileXY, q.s, false, 2);  // K0, Pi0
   force(0);
   q.xl(L_KICK, 0.5f, 0.f, kflags);
   for (int s = 1; s <= c->cur_steps; ++s) {
@@ -718,39 +804,82 @@ static hmc_status run_trajectory_learned(hmc_ctx* c) {
     force(last ? (ZF_WRITE_DRN | ZF_DATA) : 0);
     q.xl(last ? L_KICK_LAST : L_KICK, last ? 0.5f : 1.f, 0.f, kflags);
   }
-  launch_accept(c->d_all, nch, c->stream);
-  launch_commit(C_HMC, c->d_all, nch, c->total[kTileK], c->total[kTileR], c->stream);
-  return refresh_gradient(c, false);
+  launch_accept(q.d, q.nch, q.s);
+  launch_commit(C_HMC, q.d, q.nch, q.tot[kTileK], q.tot[kTileR], q.s);
+  refresh_gradient(q, false);
 }
 
-// contexts of 8^3 or 16^3 chains run a trajectory or joint move in one workgroup per chain,
-// unless the caller times the passes
-static bool one_workgroup(const hmc_ctx* c) {
-  return small_grid_supported(c->uniform_n) && !c->timing;
-}
+// contexts (and size groups) of 8^3 or 16^3 chains run a trajectory or joint move in one
+// workgroup per chain, unless the caller times the passes
+static bool one_workgroup(const Seq& q) { return small_grid_supported(q.un) && !q.c->timing; }
 
-static hmc_status run_trajectory(hmc_ctx* c) {
-  if (c->learned) return run_trajectory_learned(c);
-  Seq q = seq_all(c);
-  const int nch = (int)c->ch.size();
-  if (one_workgroup(c)) {
-    launch_small_trajectory(c->d_all, nch, c->cur_steps, c->tw, c->stream, c->uniform_n);
-    return check_launch(c);
+// one density trajectory of the chains of q (draw index from the device counter); nothing is
+// synchronised, so it can be captured in a graph
+static void trajectory(Seq& q) {
+  hmc_ctx* const c = q.c;
+  if (c->learned) return trajectory_learned(q);
+  if (one_workgroup(q)) {
+    launch_small_trajectory(q.d, q.nch, c->cur_steps, c->tw, q.s, q.un);
+    return;
   }
   q.z(Z_NOISE, 0);
   q.y(+1);
   q.x(X_START, 0.5f, 1.f, 0);
-  launch_reduce_slot(c->d_all, nch, kPartKin, kK0, kTileXY, c->stream, false, 2);  // K0, Pi0
+  launch_reduce_slot(q.d, q.nch, kPartKin, kK0, kTileXY, q.s, false, 2);  // K0, Pi0
   for (int s = 1; s < c->cur_steps; ++s) {
     q.yz(0);
     q.x(X_STEP, 1.f, 1.f, 0);
   }
   q.yz(ZF_WRITE_DRN | ZF_DATA);
   q.x(X_END, 0.5f, 0.f, 0);
-  launch_accept(c->d_all, nch, c->stream);
-  launch_commit(C_HMC, c->d_all, nch, c->total[kTileK], c->total[kTileR], c->stream);
-  return check_launch(c);
+  launch_accept(q.d, q.nch, q.s);
+  launch_commit(C_HMC, q.d, q.nch, q.tot[kTileK], q.tot[kTileR], q.s);
 }
+
+// Chains are independent for a whole trajectory or sweep, so parts of a context may run on
+// streams of their own, forked from the caller's and joined to it by events (parallel
+// branches of a captured graph): the launches of one part fill the gaps, ramps and
+// last rounds of the others'.  A batch splits into its size groups where every pass class runs
+// one launch per group (8 x 64^3, 6 x 128^3 and 2 x 192^3, sweep with the joint move: 19.5 ->
+// 16.3 ms).  A context of one size splits into halves from kSplitVoxels on: two 192^3 chains
+// 4.55 -> 3.84 ms a trajectory (their 384 planes are one and a half rounds of the compute
+// units), two 256^3 chains 6.82 -> 6.64, six 128^3 chains 2.35 -> 2.16; below it the
+// launches' own time is what a step takes (two 128^3 chains 0.92 -> 1.10, eight 64^3 chains
+// 0.85 -> 0.95, four 128^3 chains' sweeps 4.71 -> 4.88).  A chain's results do not depend on
+// its part.
+static bool split(const hmc_ctx* c) {
+  if (c->parts.size() < 2 || c->timing) return false;
+  if (c->uniform_n != 0) return !c->grid[0] && !c->grid[1] && !c->grid[2];
+  return c->grouped[0] && c->grouped[1] && c->grouped[2];
+}
+
+// f once for the whole context, or once per part on the part's stream
+static hmc_status run_parts(hmc_ctx* c, void (*f)(Seq&)) {
+  if (!split(c)) {
+    Seq q = seq_all(c);
+    f(q);
+    return check_launch(c);
+  }
+  HIPCHK(c, hipEventRecord(c->side_ev[0], c->stream));
+  hmc_status bad = HMC_OK;
+  for (size_t i = 1; i < c->parts.size(); ++i) {
+    hipStream_t st = c->side[i - 1];
+    HIPCHK(c, hipStreamWaitEvent(st, c->side_ev[0], 0));
+    Seq q = seq_part(c, c->parts[i], st);
+    f(q);
+  }
+  Seq q = seq_part(c, c->parts[0], c->stream);
+  f(q);
+  bad = check_launch(c);
+  // joined also after a failed launch, so that nothing runs past this call's place in the stream
+  for (size_t i = 1; i < c->parts.size(); ++i) {
+    HIPCHK(c, hipEventRecord(c->side_ev[i], c->side[i - 1]));
+    HIPCHK(c, hipStreamWaitEvent(c->stream, c->side_ev[i], 0));
+  }
+  return bad;
+}
+
+static hmc_status run_trajectory(hmc_ctx* c) { return run_parts(c, trajectory); }
 
 hmc_status leapfrog_trajectory(hmc_ctx* c, uint64_t traj_index, double* dH, int32_t* accepted) {
   if (!c) return fail(nullptr, HMC_EINVAL, "null context");
@@ -819,48 +948,44 @@ hmc_status shell_power(hmc_ctx* c, int32_t chain, double* sigma, int64_t* n_mode
   return HMC_OK;
 }
 
-// the device part of one block sweep for every chain (no host synchronisation)
-static hmc_status run_sweep(hmc_ctx* c) {
-  const int nch = (int)c->ch.size();
-  hmc_status st = run_trajectory(c);
-  if (st != HMC_OK) return st;
+// the device part of one block sweep of the chains of q (no host synchronisation)
+static void sweep(Seq& q) {
+  hmc_ctx* const c = q.c;
+  trajectory(q);
   // P | delta
-  launch_shell_power(c->d_all, nch, c->total[kTileK], c->stream);
-  launch_draw_power(c->d_all, nch, c->max_nb, c->stream);
+  launch_shell_power(q.d, q.nch, q.tot[kTileK], q.s);
+  launch_draw_power(q.d, q.nch, c->max_nb, q.s);
   // joint (P, delta) move for chains that ask for it (all or none in a batch)
   bool any_rj = false;
   for (auto& k : c->ch) any_rj |= k.cfg.rj_move != 0;
   if (any_rj) {
-    Seq q = seq_all(c);
     // dU at the start: per-shell Re(conj(delta_hat) g_hat) at the current state.
     // grad_k holds g_hat of delta_hat here (the trajectory's last gradient, or the
     // restored one of its start; the P draw does not change alpha, beta), so one
     // k-space pass over the stored arrays gives it.
-    launch_shell_dot(c->d_all, nch, c->total[kTileK], c->stream);
-    launch_rj(RJ_BEGIN, c->d_all, nch, c->max_nb, c->stream, kTileK);
-    if (one_workgroup(c))
-      launch_small_joint(c->d_all, nch, c->cur_steps, c->tw, c->stream, c->uniform_n);
-    for (int i = 0; !one_workgroup(c) && i < c->cur_steps; ++i) {
-      const bool last = i == c->cur_steps - 1;
-      q.gradient(last ? (ZF_WRITE_DRN | ZF_DATA) : 0,
-                 XF_SCALE | XF_DOT | (last ? XF_OUT_ALT : XF_NOSTORE));
-      if (!last) {
-        launch_rj(RJ_STEP, c->d_all, nch, c->max_nb, c->stream);
-      } else {
-        launch_rj(RJ_END, c->d_all, nch, c->max_nb, c->stream);
+    launch_shell_dot(q.d, q.nch, q.tot[kTileK], q.s);
+    launch_rj(RJ_BEGIN, q.d, q.nch, c->max_nb, q.s, kTileK);
+    if (one_workgroup(q)) {
+      launch_small_joint(q.d, q.nch, c->cur_steps, c->tw, q.s, q.un);
+    } else {
+      for (int i = 0; i < c->cur_steps; ++i) {
+        const bool last = i == c->cur_steps - 1;
+        q.gradient(last ? (ZF_WRITE_DRN | ZF_DATA) : 0,
+                   XF_SCALE | XF_DOT | (last ? XF_OUT_ALT : XF_NOSTORE));
+        launch_rj(last ? RJ_END : RJ_STEP, q.d, q.nch, c->max_nb, q.s);
       }
+      launch_commit(C_RJ, q.d, q.nch, q.tot[kTileK], q.tot[kTileR], q.s);
     }
-    if (!one_workgroup(c))
-      launch_commit(C_RJ, c->d_all, nch, c->total[kTileK], c->total[kTileR], c->stream);
-    launch_tables(c->d_all, nch, c->stream);
+    launch_tables(q.d, q.nch, q.s);
   }
   // Nbar | delta, b and b | delta, Nbar
-  launch_moments(c->d_all, nch, c->total[kTileR], c->stream);
-  launch_draw_nbar_bias(c->d_all, nch, c->max_sub, c->stream);
+  launch_moments(q.d, q.nch, q.tot[kTileR], q.s);
+  launch_draw_nbar_bias(q.d, q.nch, c->max_sub, q.s);
   // alpha, beta, mass and gradient for the new parameters
-  if ((st = refresh_coefficients(c)) != HMC_OK) return st;
-  return refresh_gradient(c, false);
+  refresh_coefficients(q);
+  refresh_gradient(q, false);
 }
+static hmc_status run_sweep(hmc_ctx* c) { return run_parts(c, sweep); }
 
 hmc_status gibbs_sweep(hmc_ctx* c, uint64_t sweep_index, hmc_sweep_stats* out) {
   if (!c) return fail(nullptr, HMC_EINVAL, "null context");
