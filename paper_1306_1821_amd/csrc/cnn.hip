@@ -172,7 +172,10 @@ __device__ __forceinline__ int brick_of(int b, int g) {
 // store wrote 2 bytes per lane).  K runs over taps, 16 channels at a time (CS = 16), or 4
 // taps x 4 channels (CS = 4: the network's input, read as float32 and rounded here).  A
 // fragment read from LDS serves every row of the wave that needs it (up to 3 of the 8):
-// 90 reads for 216 MFMAs, where one read per MFMA kept LDS as busy as the matrix cores.
+// 90 reads for 216 MFMAs, where one read per MFMA kept LDS as busy as the matrix cores.  The
+// two halves of the channels lie in separate planes of the brick, so that half a wave
+// (16 voxels x 8 channels) reads 256 bytes in a row (whole voxels of 32 bytes met every bank
+// twice: LDS was busy for 322 us of the last layer at 256^3, which went from 432 to 394 us).
 // The order of the products of one output is that of the taps, whatever the brick.
 // What bounds it at 256^3 (kernel trace): the products and the staging (396 us for the
 // last layer) and, for the hidden layers, GELU and the stores (615 us; 763 before this form
@@ -188,7 +191,7 @@ __global__ void __launch_bounds__(256, 4) k_conv(int n, const void* __restrict__
                                                  uint16_t* __restrict__ aout) {
   constexpr int kItems = CS == 16 ? 2 * kCHalo : kCHalo;  // 16-byte halves / whole voxels
   constexpr int kIter = (kItems + 255) / 256;
-  __shared__ uint4 brick[CS == 16 ? 2 * kCHalo : kCHalo / 2];  // [voxel][CS] bf16
+  __shared__ uint4 brick[CS == 16 ? 2 * kCHalo : kCHalo / 2];  // [channel half][voxel] / [voxel][4]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int nbz = (n + kBZ - 1) / kBZ, nby = (n + kCY - 1) / kCY;
   const int bk = brick_of(blockIdx.x, gridDim.x);
@@ -220,7 +223,7 @@ __global__ void __launch_bounds__(256, 4) k_conv(int n, const void* __restrict__
     const int i = threadIdx.x + 256 * k;
     if (i < kItems) {
       if constexpr (CS == 16)
-        brick[i] = st[k];
+        brick[(i & 1) * kCHalo + (i >> 1)] = st[k];
       else
         reinterpret_cast<ushort4*>(brick)[i] = make_ushort4(f2bf(sf[k][0]), f2bf(sf[k][1]), f2bf(sf[k][2]), 0);
     }
@@ -228,6 +231,7 @@ __global__ void __launch_bounds__(256, 4) k_conv(int n, const void* __restrict__
   __syncthreads();
   const int m = lane & 15, grp = lane >> 4;
   const bf16x4* lb = reinterpret_cast<const bf16x4*>(brick);
+  const int ofs = (grp >> 1) * 2 * kCHalo + (grp & 1);  // the lane's 4 channels (CS = 16)
   f32x4 acc[kCY];
 #pragma unroll
   for (int r = 0; r < kCY; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -238,7 +242,7 @@ __global__ void __launch_bounds__(256, 4) k_conv(int n, const void* __restrict__
       for (int hy = 0; hy < kCHY; ++hy)
 #pragma unroll
         for (int dz = 0; dz < 3; ++dz) {
-          const bf16x4 b = lb[(((wave + dx) * kCHY + hy) * kHZ + m + dz) * 4 + grp];
+          const bf16x4 b = lb[(((wave + dx) * kCHY + hy) * kHZ + m + dz) * 2 + ofs];
 #pragma unroll
           for (int r = 0; r < kCY; ++r)
             if (r <= hy && hy <= r + 2)
@@ -310,20 +314,20 @@ __global__ void __launch_bounds__(256) k_loss(long long nv, const float2* __rest
 // Weight gradient: dW[t][ci][co] = sum_v a[v + d_t][ci] dz[v][co], the MFMA's K over 16
 // voxels of a z row (B = dz, columns co).  A block walks bricks of BX x BY x 16 voxels and
 // stages them channel-major in LDS, the activations with their halo; a staging thread turns
-// 4 voxels x 4 channels (8-byte loads and LDS writes).  The channel pitches are 8 mod 64
-// words, so that a fragment read (16 channels x 4 voxel quads) meets every bank twice, its
-// minimum.  Wave w owns 4 rows; an input row is read once (an aligned quad and the two voxels
+// 4 voxels x 4 channels (8-byte loads and LDS writes).  The channel pitches are an odd
+// multiple of 4 words, so that half a wave's fragment reads (16 channels x 2 voxel quads of
+// 2 words) meet every one of the 64 banks once.  Wave w owns 4 rows; an input row is read once (an aligned quad and the two voxels
 // after it) and gives the fragments of all three z shifts in registers for every row of the
 // wave it is a neighbour of: 36 reads for 108 MFMAs, where each fragment took four 2-byte
 // reads.  CS = 16: A rows are the input channels of one tap.  CS = 4: A rows are (z shift,
 // channel), 9 MFMAs a row instead of 27, read from the network's float32 input.  The
 // waves' sums meet in LDS, one partial per block, summed by k_wreduce in a fixed order.
-// 128^3: 74 us a 16-channel layer and 68 us for the first (103 and 202 us before); the
+// 128^3: 72 us a 16-channel layer and 66 us for the first (103 and 202 us before); the
 // accumulators (108 registers) leave 3 blocks per compute unit.
 constexpr int kBX = 2, kBY = 8;
 constexpr int kHX = kBX + 2, kHY = kBY + 2, kRowP = 20;  // halo rows hold 18 voxels of 20
-constexpr int kChA = kHX * kHY * kRowP + 16, kChD = kBX * kBY * kBZ + 16;  // channel pitches
-static_assert(kChA / 2 % 64 == 24 && kChD / 2 % 64 == 8 && kChA % 4 == 0, "channel pitches");
+constexpr int kChA = kHX * kHY * kRowP + 8, kChD = kBX * kBY * kBZ + 8;  // channel pitches
+static_assert(kChA / 2 % 8 == 4 && kChD / 2 % 8 == 4 && kChA % 4 == 0, "channel pitches");
 
 // 4 channels of 4 voxels -> 4 voxels of 4 channels
 __device__ __forceinline__ void turn4(const uint2* v, uint2* c) {
