@@ -63,18 +63,17 @@ __device__ __forceinline__ float gelu_grad(float z) {
 // weighted least-squares fit iterated towards equal ripples).  Evaluated in float32 the value is
 // within kErr0 + kErr1 y^2 (relative; for GELU' times the magnitudes of the two terms it
 // adds) of the erfcf form above; where no bf16 rounding boundary lies within that distance,
-// both round to the same bf16 value, else (about one value in 1300), and outside the range of
+// both round to the same bf16 value, else (about one value in 950), and outside the range of
 // the bound (y >= 10, tiny, huge or not finite), the erfcf form decides.  Checked against it for
 // every float32 z: the largest deviation is two thirds of the bound.  erfcf is about 50
 // instructions, three of them quarter rate, and at 256^3 a layer evaluates it 268 million
-// times: a hidden layer went from 713 to 615 us and the first from 511 to 372 us.
+// times: a hidden layer went from 713 to 562 us and the first from 511 to 380 us.
 constexpr float kErr0 = 9e-7f, kErr1 = 3.75e-7f;
 struct Cdf {
-  float phi, e, err;  // Phi(z), exp(-z^2 / 2), the relative bound
-  bool ok;
+  float q, e, y2;  // Phi(-|z|), exp(-z^2 / 2), z^2
 };
 __device__ __forceinline__ Cdf norm_cdf_short(float z) {
-  const float y = fabsf(z), t = __builtin_amdgcn_rcpf(__builtin_fmaf(0.3f, y, 1.f)), y2 = y * y;
+  const float t = __builtin_amdgcn_rcpf(__builtin_fmaf(0.3f, fabsf(z), 1.f));
   float p = 0.037548013f;
   p = __builtin_fmaf(p, t, -0.165077418f);
   p = __builtin_fmaf(p, t, 0.220085055f);
@@ -84,11 +83,9 @@ __device__ __forceinline__ Cdf norm_cdf_short(float z) {
   p = __builtin_fmaf(p, t, 0.121111214f);
   p = __builtin_fmaf(p, t, 0.119605042f);
   Cdf c;
-  c.e = __builtin_amdgcn_exp2f(-0.721347520444481704f * y2);
-  const float q = c.e * (t * p);
-  c.phi = z > 0.f ? 1.f - q : q;
-  c.err = __builtin_fmaf(kErr1, y2, kErr0);
-  c.ok = y2 < 100.f;
+  c.y2 = z * z;
+  c.e = __builtin_amdgcn_exp2f(-0.721347520444481704f * c.y2);
+  c.q = c.e * (t * p);
   return c;
 }
 // true if r - b and r + b (b >= 0) round to the same bf16 value
@@ -97,15 +94,20 @@ __device__ __forceinline__ bool same_bf(float r, float b) {
 }
 __device__ __forceinline__ bool plain(float r) { return fabsf(r) > 1e-30f && fabsf(r) < 1e30f; }
 
+// GELU(z) = max(z, 0) - |z| Phi(-|z|); the distance of its low 16 bits from a rounding boundary
+// is compared with the bound in units of the last place (at most 2^-23 of the value)
 __device__ __forceinline__ ushort4 gelu_bf4(const float* z) {
   uint16_t o[4];
   bool ok[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const Cdf c = norm_cdf_short(z[i]);
-    const float r = z[i] * c.phi;
-    ok[i] = c.ok && plain(r) && same_bf(r, fabsf(r) * c.err);
-    o[i] = (uint16_t)((__float_as_uint(r) + 0x8000u) >> 16);
+    const uint32_t u = __float_as_uint(__builtin_fmaf(-fabsf(z[i]), c.q, fmaxf(z[i], 0.f)));
+    const float d = (float)(int)(int16_t)(uint16_t)(u ^ 0x8000u);
+    // 1e-12 < z^2 < 100 (as integers; also false for NaN)
+    const bool in = __float_as_uint(c.y2) - 0x2b8cbcccu < 0x42c80000u - 0x2b8cbcccu;
+    ok[i] = in && fabsf(d) > __builtin_fmaf(kErr1 * 16777216.f, c.y2, kErr0 * 16777216.f);
+    o[i] = (uint16_t)((u + 0x8000u) >> 16);
   }
   if (!(ok[0] && ok[1] && ok[2] && ok[3])) {
 #pragma unroll
@@ -121,8 +123,9 @@ __device__ __forceinline__ ushort4 gelu_grad_bf4(const float* v, const float* z)
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const Cdf c = norm_cdf_short(z[i]);
-    const float zp = z[i] * (c.e * 0.3989422804014327f), r = v[i] * (c.phi + zp);
-    ok[i] = c.ok && plain(r) && same_bf(r, fabsf(v[i]) * (c.err * (c.phi + fabsf(zp))));
+    const float phi = z[i] > 0.f ? 1.f - c.q : c.q, err = __builtin_fmaf(kErr1, c.y2, kErr0);
+    const float zp = z[i] * (c.e * 0.3989422804014327f), r = v[i] * (phi + zp);
+    ok[i] = c.y2 < 100.f && plain(r) && same_bf(r, fabsf(v[i]) * (err * (phi + fabsf(zp))));
     o[i] = (uint16_t)((__float_as_uint(r) + 0x8000u) >> 16);
   }
   if (!(ok[0] && ok[1] && ok[2] && ok[3])) {
