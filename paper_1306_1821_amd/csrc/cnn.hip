@@ -25,6 +25,7 @@
 namespace cnnk {
 
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kCin[4] = {3, 16, 16, 16};
@@ -179,10 +180,18 @@ __device__ __forceinline__ int brick_of(int b, int g) {
 // two halves of the channels lie in separate planes of the brick, so that half a wave
 // (16 voxels x 8 channels) reads 256 bytes in a row (whole voxels of 32 bytes met every bank
 // twice: LDS was busy for 322 us of the last layer at 256^3, which went from 432 to 394 us).
-// The order of the products of one output is that of the taps, whatever the brick.
-// What bounds it at 256^3 (kernel trace): the products and the staging (396 us for the
-// last layer) and, for the hidden layers, GELU and the stores (615 us; 763 before this form
-// and gelu_bf4, and the last layer 661 us plus 257 us to pick its two channels out of 16).
+// The order of the products of one output is the same for every brick and voxel: that of
+// the taps, except in the last layer.  That one has two output channels, which left 14 of
+// the 16 matrix rows empty: its rows are (y tap, channel), one accumulator tile for each of
+// the 10 haloed rows, and K is 32, two taps of 16 channels at once (a lane reads the 8
+// channels of one plane of the brick): 50 MFMAs and 50 reads a wave instead of 216 and 90;
+// an output is the sum of three rows of three tiles.  Its float32 sums take another order
+// for that (the hidden layers keep theirs, as their results are rounded to bfloat16).
+// What bounds it at 256^3: for the hidden layers the products, GELU and the stores (562 us;
+// 763 before this form and the short GELU), for the last layer the staging (289 us;
+// 382 with its two channels as rows, 661 plus 257 us to pick its two channels out of 16
+// before that).  A forward at 256^3 went from 1648 to 1540 us with the last layer's form, a
+// training step at 128^3 from 924 to 910.
 // TRAIN: keep the pre-activation for the backward pass.  LAST: out0, out1 are the two
 // output channels, or out0 the pairs [V][2] for the loss (TRAIN).
 template <int CS, int MODE, bool TRAIN>
@@ -217,8 +226,14 @@ __global__ void __launch_bounds__(256, 4) k_conv(int n, const void* __restrict__
       for (int c = 0; c < 3; ++c) sf[k][c] = ok ? reinterpret_cast<const float*>(in)[c * nv + v] : 0.f;
     }
   }
-  constexpr int NC = CS == 16 ? 27 : 7;
+  constexpr int NC = MODE == C_FWD_LAST ? 1 : CS == 16 ? 27 : 7;
   bf16x4 w[NC];
+  bf16x8 w2[MODE == C_FWD_LAST ? 4 : 1];
+  if constexpr (MODE == C_FWD_LAST) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) w2[c] = reinterpret_cast<const bf16x8*>(wp)[c * 64 + lane];
+    wp += 8 * 64;
+  }
 #pragma unroll
   for (int c = 0; c < NC; ++c) w[c] = wp[c * 64 + lane];
 #pragma unroll
@@ -235,10 +250,32 @@ __global__ void __launch_bounds__(256, 4) k_conv(int n, const void* __restrict__
   const int m = lane & 15, grp = lane >> 4;
   const bf16x4* lb = reinterpret_cast<const bf16x4*>(brick);
   const int ofs = (grp >> 1) * 2 * kCHalo + (grp & 1);  // the lane's 4 channels (CS = 16)
-  f32x4 acc[kCY];
+  constexpr int kRows = MODE == C_FWD_LAST ? kCHY : kCY;
+  f32x4 acc[kRows];
 #pragma unroll
-  for (int r = 0; r < kCY; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
-  if constexpr (CS == 16) {
+  for (int r = 0; r < kRows; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if constexpr (MODE == C_FWD_LAST) {
+    // tap pairs (dz 0, 1) of each dx, then dz = 2 of dx 0, 1; a lane reads 8 channels of one
+    const int half = (grp & 1) * kCHalo, second = grp >> 1;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int at = c < 3 ? (wave + c) * kCHY * kHZ + m + second : (wave + second) * kCHY * kHZ + m + 2;
+#pragma unroll
+      for (int hy = 0; hy < kCHY; ++hy)
+        acc[hy] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            w2[c], __builtin_bit_cast(bf16x8, brick[half + at + hy * kHZ]), acc[hy], 0, 0, 0);
+    }
+#pragma unroll
+    for (int hy = 0; hy < kCHY; ++hy)  // dx = 2, dz = 2
+      acc[hy] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(
+          w[0], lb[(((wave + 2) * kCHY + hy) * kHZ + m + 2) * 2 + ofs], acc[hy], 0, 0, 0);
+    // rows (dy, channel): dy 0 and 1 in the lanes of group 0, dy 2 in those of group 1
+#pragma unroll
+    for (int r = 0; r < kCY; ++r)
+#pragma unroll
+      for (int o = 0; o < 2; ++o)
+        acc[r][o] = (acc[r][o] + acc[r + 1][2 + o]) + __shfl_xor(acc[r + 2][o], 16);
+  } else if constexpr (CS == 16) {
 #pragma unroll
     for (int dx = 0; dx < 3; ++dx)
 #pragma unroll
@@ -541,7 +578,8 @@ __global__ void __launch_bounds__(256) k_adam(int np, float* __restrict__ p, con
   p[i] -= lr * (m1[i] / c1) / (sqrtf(m2[i] / c2) + 1e-8f);
 }
 
-// bf16 MFMA B operands of one layer: forward (wp) and mirrored/transposed (wd).
+// bf16 MFMA operands of one layer: forward (wp; the last layer's in k_conv's own order,
+// k_pack_last) and mirrored/transposed (wd).
 __global__ void __launch_bounds__(256) k_pack(const float* __restrict__ W, int cin, int cout,
                                               int forward, int nchunk, bf16x4* __restrict__ out) {
   const int idx = blockIdx.x * 256 + threadIdx.x;
@@ -567,6 +605,24 @@ __global__ void __launch_bounds__(256) k_pack(const float* __restrict__ W, int c
     }
     r[i] = (short)f2bf(w);
   }
+  out[idx] = r;
+}
+
+// The last layer's A operand: rows (dy, channel), 4 pairs of taps (8 channels of one a lane),
+// then the tap (dx, dz) = (2, 2) alone.
+constexpr int kLastChunks = 9;  // of 64 bf16x4
+__global__ void __launch_bounds__(256) k_pack_last(const float* __restrict__ W, bf16x4* __restrict__ out) {
+  const int idx = blockIdx.x * 256 + threadIdx.x;
+  if (idx >= kLastChunks * 64) return;
+  const bool pair = idx < 8 * 64;
+  const int c = idx / 128, lane = pair ? idx % 128 / 2 : idx % 64;
+  const int row = lane % 16, dy = row / 2, co = row % 2, grp = lane / 16;
+  const int dx = !pair ? 2 : c < 3 ? c : grp / 2, dz = pair && c < 3 ? grp / 2 : 2;
+  const int ci = pair ? 8 * (grp % 2) + 4 * (idx % 2) : 4 * grp;
+  bf16x4 r;
+  for (int i = 0; i < 4; ++i)
+    r[i] = dy < 3 ? (short)f2bf(W[(((dx * 3 + dy) * 3 + dz) * kCin[3] + ci + i) * kCout[3] + co])
+                  : (short)0;
   out[idx] = r;
 }
 
@@ -610,13 +666,17 @@ hmc_status cfail(cnn_ctx* c, hmc_status st, const std::string& why) {
     if (e_ != hipSuccess) return cfail(c, HMC_EDEVICE, std::string(#call) + ": " + hipGetErrorString(e_)); \
   } while (0)
 
-int nchunk_fwd(int l) { return l == 0 ? 7 : 27; }
+int nchunk_fwd(int l) { return l == 0 ? 7 : l == 3 ? kLastChunks : 27; }
 
 hmc_status pack_all(cnn_ctx* c) {
   for (int l = 0; l < 4; ++l) {
     const int nc = nchunk_fwd(l);
-    hipLaunchKernelGGL(k_pack, dim3((nc * 64 + 255) / 256), dim3(256), 0, c->stream,
-                       c->p + off_w(l), kCin[l], kCout[l], 1, nc, c->wp[l]);
+    if (l == 3)
+      hipLaunchKernelGGL(k_pack_last, dim3((nc * 64 + 255) / 256), dim3(256), 0, c->stream,
+                         c->p + off_w(l), c->wp[l]);
+    else
+      hipLaunchKernelGGL(k_pack, dim3((nc * 64 + 255) / 256), dim3(256), 0, c->stream,
+                         c->p + off_w(l), kCin[l], kCout[l], 1, nc, c->wp[l]);
     if (l > 0)
       hipLaunchKernelGGL(k_pack, dim3((27 * 64 + 255) / 256), dim3(256), 0, c->stream,
                          c->p + off_w(l), kCin[l], kCout[l], 0, 27, c->wd[l]);
