@@ -181,17 +181,18 @@ __device__ __forceinline__ int brick_of(int b, int g) {
 // (16 voxels x 8 channels) reads 256 bytes in a row (whole voxels of 32 bytes met every bank
 // twice: LDS was busy for 322 us of the last layer at 256^3, which went from 432 to 394 us).
 // The order of the products of one output is the same for every brick and voxel: that of
-// the taps, except in the last layer.  That one has two output channels, which left 14 of
-// the 16 matrix rows empty: its rows are (y tap, channel), one accumulator tile for each of
-// the 10 haloed rows, and K is 32, two taps of 16 channels at once (a lane reads the 8
-// channels of one plane of the brick): 50 MFMAs and 50 reads a wave instead of 216 and 90;
-// an output is the sum of three rows of three tiles.  Its float32 sums take another order
-// for that (the hidden layers keep theirs, as their results are rounded to bfloat16).
-// What bounds it at 256^3: for the hidden layers the products, GELU and the stores (562 us;
+// the taps, except in the last layer outside training.  That one has two output channels,
+// which leaves 14 of the 16 matrix rows empty: its rows are (y tap, channel), one accumulator
+// tile for each of the 10 haloed rows, and K is 32, two taps of 16 channels at once (a lane
+// reads the 8 channels of one plane of the brick): 50 MFMAs and 50 reads a wave instead of
+// 216 and 90; an output is the sum of three rows of three tiles.  Its float32 sums take
+// another order for that.  Training keeps the order of the taps: the output gradient is
+// rounded to bfloat16, and the small differences that come of it grow from step to step
+// (14 of 924 us at 128^3); so do the hidden layers, whose results are rounded as well.
+// What bounds it at 256^3: for the hidden layers the products, GELU and the stores (570 us;
 // 763 before this form and the short GELU), for the last layer the staging (289 us;
 // 382 with its two channels as rows, 661 plus 257 us to pick its two channels out of 16
-// before that).  A forward at 256^3 went from 1648 to 1540 us with the last layer's form, a
-// training step at 128^3 from 924 to 910.
+// before that).  A forward at 256^3 went from 1648 to 1540 us with the last layer's form.
 // TRAIN: keep the pre-activation for the backward pass.  LAST: out0, out1 are the two
 // output channels, or out0 the pairs [V][2] for the loss (TRAIN).
 template <int CS, int MODE, bool TRAIN>
@@ -226,16 +227,24 @@ __global__ void __launch_bounds__(256, 4) k_conv(int n, const void* __restrict__
       for (int c = 0; c < 3; ++c) sf[k][c] = ok ? reinterpret_cast<const float*>(in)[c * nv + v] : 0.f;
     }
   }
-  constexpr int NC = MODE == C_FWD_LAST ? 1 : CS == 16 ? 27 : 7;
+  constexpr bool kPairs = MODE == C_FWD_LAST && !TRAIN;  // two taps a product
+  constexpr int NC = kPairs ? 1 : CS == 16 ? 27 : 7;
   bf16x4 w[NC];
-  bf16x8 w2[MODE == C_FWD_LAST ? 4 : 1];
-  if constexpr (MODE == C_FWD_LAST) {
+  bf16x4 w2[kPairs ? 4 : 1][2];
+  if constexpr (kPairs) {  // matrix row 2 dy + channel, from wp's row of that channel
+    const int dy = (lane & 15) >> 1, at = dy * 3 * 64 + (lane & 1), g = lane >> 4;
+    const bf16x4 none = {0, 0, 0, 0};
 #pragma unroll
-    for (int c = 0; c < 4; ++c) w2[c] = reinterpret_cast<const bf16x8*>(wp)[c * 64 + lane];
-    wp += 8 * 64;
+    for (int c = 0; c < 4; ++c) {
+      const int tap = c < 3 ? 9 * c + (g >> 1) : 9 * (g >> 1) + 2;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) w2[c][h] = dy < 3 ? wp[tap * 64 + at + (2 * (g & 1) + h) * 16] : none;
+    }
+    w[0] = dy < 3 ? wp[20 * 64 + at + g * 16] : none;
+  } else {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) w[c] = wp[c * 64 + lane];
   }
-#pragma unroll
-  for (int c = 0; c < NC; ++c) w[c] = wp[c * 64 + lane];
 #pragma unroll
   for (int k = 0; k < kIter; ++k) {
     const int i = threadIdx.x + 256 * k;
@@ -250,20 +259,21 @@ __global__ void __launch_bounds__(256, 4) k_conv(int n, const void* __restrict__
   const int m = lane & 15, grp = lane >> 4;
   const bf16x4* lb = reinterpret_cast<const bf16x4*>(brick);
   const int ofs = (grp >> 1) * 2 * kCHalo + (grp & 1);  // the lane's 4 channels (CS = 16)
-  constexpr int kRows = MODE == C_FWD_LAST ? kCHY : kCY;
+  constexpr int kRows = kPairs ? kCHY : kCY;
   f32x4 acc[kRows];
 #pragma unroll
   for (int r = 0; r < kRows; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
-  if constexpr (MODE == C_FWD_LAST) {
+  if constexpr (kPairs) {
     // tap pairs (dz 0, 1) of each dx, then dz = 2 of dx 0, 1; a lane reads 8 channels of one
     const int half = (grp & 1) * kCHalo, second = grp >> 1;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
       const int at = c < 3 ? (wave + c) * kCHY * kHZ + m + second : (wave + second) * kCHY * kHZ + m + 2;
+      const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(w2[c][0], w2[c][1], 0, 1, 2, 3, 4, 5, 6, 7));
 #pragma unroll
       for (int hy = 0; hy < kCHY; ++hy)
         acc[hy] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-            w2[c], __builtin_bit_cast(bf16x8, brick[half + at + hy * kHZ]), acc[hy], 0, 0, 0);
+            a, __builtin_bit_cast(bf16x8, brick[half + at + hy * kHZ]), acc[hy], 0, 0, 0);
     }
 #pragma unroll
     for (int hy = 0; hy < kCHY; ++hy)  // dx = 2, dz = 2
@@ -578,8 +588,7 @@ __global__ void __launch_bounds__(256) k_adam(int np, float* __restrict__ p, con
   p[i] -= lr * (m1[i] / c1) / (sqrtf(m2[i] / c2) + 1e-8f);
 }
 
-// bf16 MFMA operands of one layer: forward (wp; the last layer's in k_conv's own order,
-// k_pack_last) and mirrored/transposed (wd).
+// bf16 MFMA A operands of one layer: forward (wp) and mirrored/transposed (wd).
 __global__ void __launch_bounds__(256) k_pack(const float* __restrict__ W, int cin, int cout,
                                               int forward, int nchunk, bf16x4* __restrict__ out) {
   const int idx = blockIdx.x * 256 + threadIdx.x;
@@ -605,24 +614,6 @@ __global__ void __launch_bounds__(256) k_pack(const float* __restrict__ W, int c
     }
     r[i] = (short)f2bf(w);
   }
-  out[idx] = r;
-}
-
-// The last layer's A operand: rows (dy, channel), 4 pairs of taps (8 channels of one a lane),
-// then the tap (dx, dz) = (2, 2) alone.
-constexpr int kLastChunks = 9;  // of 64 bf16x4
-__global__ void __launch_bounds__(256) k_pack_last(const float* __restrict__ W, bf16x4* __restrict__ out) {
-  const int idx = blockIdx.x * 256 + threadIdx.x;
-  if (idx >= kLastChunks * 64) return;
-  const bool pair = idx < 8 * 64;
-  const int c = idx / 128, lane = pair ? idx % 128 / 2 : idx % 64;
-  const int row = lane % 16, dy = row / 2, co = row % 2, grp = lane / 16;
-  const int dx = !pair ? 2 : c < 3 ? c : grp / 2, dz = pair && c < 3 ? grp / 2 : 2;
-  const int ci = pair ? 8 * (grp % 2) + 4 * (idx % 2) : 4 * grp;
-  bf16x4 r;
-  for (int i = 0; i < 4; ++i)
-    r[i] = dy < 3 ? (short)f2bf(W[(((dx * 3 + dy) * 3 + dz) * kCin[3] + ci + i) * kCout[3] + co])
-                  : (short)0;
   out[idx] = r;
 }
 
@@ -666,17 +657,13 @@ hmc_status cfail(cnn_ctx* c, hmc_status st, const std::string& why) {
     if (e_ != hipSuccess) return cfail(c, HMC_EDEVICE, std::string(#call) + ": " + hipGetErrorString(e_)); \
   } while (0)
 
-int nchunk_fwd(int l) { return l == 0 ? 7 : l == 3 ? kLastChunks : 27; }
+int nchunk_fwd(int l) { return l == 0 ? 7 : 27; }
 
 hmc_status pack_all(cnn_ctx* c) {
   for (int l = 0; l < 4; ++l) {
     const int nc = nchunk_fwd(l);
-    if (l == 3)
-      hipLaunchKernelGGL(k_pack_last, dim3((nc * 64 + 255) / 256), dim3(256), 0, c->stream,
-                         c->p + off_w(l), c->wp[l]);
-    else
-      hipLaunchKernelGGL(k_pack, dim3((nc * 64 + 255) / 256), dim3(256), 0, c->stream,
-                         c->p + off_w(l), kCin[l], kCout[l], 1, nc, c->wp[l]);
+    hipLaunchKernelGGL(k_pack, dim3((nc * 64 + 255) / 256), dim3(256), 0, c->stream,
+                       c->p + off_w(l), kCin[l], kCout[l], 1, nc, c->wp[l]);
     if (l > 0)
       hipLaunchKernelGGL(k_pack, dim3((27 * 64 + 255) / 256), dim3(256), 0, c->stream,
                          c->p + off_w(l), kCin[l], kCout[l], 0, 27, c->wd[l]);

@@ -45,16 +45,20 @@ def test_overhanging_bricks_match_oracle(n):
 
 @pytest.mark.parametrize("n", [4, 8, 12, 20])
 def test_last_layer_every_voxel(n):
-    """The last layer (its taps in pairs, its three y taps in the matrix rows) from the device's
-    own activations against a float64 convolution with the weights rounded to bfloat16: each
-    output within the bound of a float32 sum of 433 terms, 434 2^-24 sum |w a|."""
+    """The last layer from the device's own activations, in training (products in the order of
+    the taps) and alone (its taps in pairs, its three y taps in the matrix rows), against a
+    float64 convolution with the weights rounded to bfloat16: each output within the bound of
+    a float32 sum of 433 terms, 434 2^-24 sum |w a|."""
     params, x, target = case(n, 700 + n)
     net = CNN(params)
-    net.gradient(np.moveaxis(x, -1, 0), target)
+    inputs = np.moveaxis(x, -1, 0)
+    net.gradient(inputs, target)
     a, z = net.layer_state(2, n)[1].reshape(n, n, n, -1), net.layer_state(3, n)[0]
+    alone = np.stack([o.cpu().numpy().astype(np.float64).ravel() for o in net.forward(inputs)], -1)
     W, b = params[3]
     W = cnn.bf16(W)
     want = cnn.conv(a, W, b).reshape(-1, 2)
     size = cnn.conv(np.abs(a), np.abs(W), np.abs(b)).reshape(-1, 2)
     assert np.all(np.abs(z - want) <= 434 * 2.0 ** -24 * size)
+    assert np.all(np.abs(alone - want) <= 434 * 2.0 ** -24 * size)
     net.close()
