@@ -861,22 +861,32 @@ static hmc_status run_parts(hmc_ctx* c, void (*f)(Seq&)) {
     return check_launch(c);
   }
   HIPCHK(c, hipEventRecord(c->side_ev[0], c->stream));
-  hmc_status bad = HMC_OK;
-  for (size_t i = 1; i < c->parts.size(); ++i) {
-    hipStream_t st = c->side[i - 1];
-    HIPCHK(c, hipStreamWaitEvent(st, c->side_ev[0], 0));
-    Seq q = seq_part(c, c->parts[i], st);
+  // after a failed call no further part starts, and the parts that run are still joined, so
+  // that nothing runs past this call's place in the stream
+  hmc_status st = HMC_OK;
+  auto ok = [&](hipError_t e, const char* what) {
+    if (e == hipSuccess) return true;
+    (void)hipGetLastError();  // reported here, not by the next call
+    if (st == HMC_OK) st = fail(c, HMC_EDEVICE, std::string(what) + ": " + hipGetErrorString(e));
+    return false;
+  };
+  size_t running = 0;  // side streams with a part on them
+  while (running + 1 < c->parts.size() &&
+         ok(hipStreamWaitEvent(c->side[running], c->side_ev[0], 0), "fork of a part")) {
+    Seq q = seq_part(c, c->parts[running + 1], c->side[running]);
     f(q);
+    ++running;
   }
-  Seq q = seq_part(c, c->parts[0], c->stream);
-  f(q);
-  bad = check_launch(c);
-  // joined also after a failed launch, so that nothing runs past this call's place in the stream
-  for (size_t i = 1; i < c->parts.size(); ++i) {
-    HIPCHK(c, hipEventRecord(c->side_ev[i], c->side[i - 1]));
-    HIPCHK(c, hipStreamWaitEvent(c->stream, c->side_ev[i], 0));
+  if (st == HMC_OK) {
+    Seq q = seq_part(c, c->parts[0], c->stream);
+    f(q);
+    st = check_launch(c);
   }
-  return bad;
+  for (size_t i = 0; i < running; ++i)
+    if (!ok(hipEventRecord(c->side_ev[i + 1], c->side[i]), "end of a part") ||
+        !ok(hipStreamWaitEvent(c->stream, c->side_ev[i + 1], 0), "join of a part"))
+      (void)hipStreamSynchronize(c->side[i]);
+  return st;
 }
 
 static hmc_status run_trajectory(hmc_ctx* c) { return run_parts(c, trajectory); }
