@@ -233,7 +233,9 @@ hmc_status hmc_warm_start(hmc_ctx* ctx, int32_t chain, const float* mu_dev,
  * multiple of 8 keeps each XCD on a contiguous run of tiles), 0 for one
  * workgroup per tile (the default), or -1 for one single-size launch per grid
  * size of a mixed-size batch (one workgroup per tile each; the same as 0 when
- * every chain has one size).  Results do not depend on it. */
+ * every chain has one size).  Results do not depend on it bit for bit, but for one
+ * thing: with -1 for the y and the real-space class the size groups of a batch run
+ * the plane pass where they have one (hmc_set_plane_pass: float32 rounding). */
 hmc_status hmc_set_launch(hmc_ctx* ctx, int32_t pass_class, int32_t grid);
 
 /* Radix plan of the transforms of a pass class (0 the k-space step pass, 1 the
@@ -258,7 +260,8 @@ hmc_status hmc_set_plan(hmc_ctx* ctx, int32_t pass_class, int32_t plan);
  * inverse y transforms, the C2R z transforms, the data force of eq.
  * Wiener_Posterior_force, the R2C z transforms and the forward y transforms
  * with the plane on chip, so a leapfrog step moves 40 N^3 instead of 56 N^3
- * bytes.  Results agree with the separate passes to float32 rounding, not
+ * bytes.  The real-space parts of a learned mass's step run as plane passes under the
+ * same conditions.  Results agree with the separate passes to float32 rounding, not
  * bitwise.  Captured graphs are dropped.  HMC_EINVAL unless enable is 0 or 1. */
 hmc_status hmc_set_plane_pass(hmc_ctx* ctx, int32_t enable);
 

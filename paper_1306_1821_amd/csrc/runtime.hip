@@ -314,9 +314,7 @@ struct Seq {
       tm.done(s);
       return;
     }
-    bool some = false;
-    for (auto& g : c->groups) some |= plane_pass_batches(g.n);
-    if (c->plane_pass && un == 0 && c->grouped[1] && c->grouped[2] && some) {
+    if (group_planes()) {
       Timed tm(c, 2, s);
       for (auto& g : c->groups) {
         if (plane_pass_batches(g.n)) {
@@ -337,6 +335,13 @@ struct Seq {
   }
   bool planes() const {
     return c->plane_pass && un != 0 && (batch ? plane_pass_batches(un) : plane_pass_supported(un));
+  }
+  // a whole batch whose y and real-space passes run one launch per size group, some of which
+  // have a plane pass
+  bool group_planes() const {
+    if (!c->plane_pass || un != 0 || !c->grouped[1] || !c->grouped[2]) return false;
+    return std::any_of(c->groups.begin(), c->groups.end(),
+                       [](const hmc_ctx::Group& g) { return plane_pass_batches(g.n); });
   }
   void yzl(int kind, int zflags) {
     Timed tm(c, 3, s);
@@ -769,6 +774,15 @@ hmc_status hmc_init(const hmc_config* cfg, const hmc_buffers* buf, const double*
 // kernels.hip); the plain gradient cache is refreshed after the Metropolis test
 static void trajectory_learned(Seq& q) {
   hmc_ctx* const c = q.c;
+  // size groups with plane passes take them also where the batch is not divided (pass timing,
+  // x passes in one launch), so that the form, and with it the rounding, is the same
+  if (q.group_planes()) {
+    for (auto& g : c->groups) {
+      Seq p = seq_part(c, g, q.s);
+      trajectory_learned(p);
+    }
+    return;
+  }
   // the plane passes where the context has them (T, T2, T3 one round trip each), else the
   // separate y, z, y passes
   const bool planes = q.planes();

@@ -1,5 +1,7 @@
 """Which kernels a context launches, on which streams, and how these are joined: against a HIP
 runtime that only writes down what it is asked (no GPU)."""
+import re
+
 import pytest
 
 import hip_record as hr
@@ -28,3 +30,26 @@ def test_parts_are_joined_when_a_call_fails(call, nth):
     assert "refused" in why
     assert hr.unjoined(log) == []
     assert st2 == binding.HMC_OK and len(hr.streams(after)) == 4 and hr.unjoined(after) == []
+
+
+def learned_forms(launch):
+    c = hr.Context(GROUPS)
+    for cls in range(3):
+        c.check(hr.lib.hmc_set_launch(c.ctx, cls, launch[cls]))
+    c.learned()
+    out = [c.log()]
+    c.timing(True)
+    out.append(c.log())
+    c.graph(True)
+    out.append(c.log())
+    kinds = re.compile(r"yzpass_n.*ELi[123]EE")   # the learned mass's, not the plain data force (0)
+    return [sorted(k for k in hr.kernels(log) if kinds.search(k)) for log, _ in out]
+
+
+@pytest.mark.parametrize("launch,planes", [((-1, -1, -1), True), ((0, -1, -1), True), ((0, 0, 0), False), ((-1, 0, -1), False)])
+def test_learned_mass_batch_has_one_form(launch, planes):
+    """The passes a learned mass takes in a batch of several sizes follow from its launches
+    alone: the same plane passes with pass timing on, off, and captured."""
+    direct, timed, captured = hr.call(learned_forms, launch)
+    assert bool(direct) == planes
+    assert direct == timed == captured
