@@ -235,7 +235,12 @@ hmc_status hmc_warm_start(hmc_ctx* ctx, int32_t chain, const float* mu_dev,
  * size of a mixed-size batch (one workgroup per tile each; the same as 0 when
  * every chain has one size).  Results do not depend on it bit for bit, but for one
  * thing: with -1 for the y and the real-space class the size groups of a batch run
- * the plane pass where they have one (hmc_set_plane_pass: float32 rounding). */
+ * the plane pass where they have one (hmc_set_plane_pass: float32 rounding).
+ * Chains advance in parts, each on a stream of its own between the call's start and
+ * end in the caller's stream: the size groups of a batch while all three classes are
+ * at -1, and the two halves of a context of one size (128^3 up, at least two chains and
+ * 12 million voxels) while all three are at 0 or -1.  Any other setting keeps all
+ * chains on the caller's stream. */
 hmc_status hmc_set_launch(hmc_ctx* ctx, int32_t pass_class, int32_t grid);
 
 /* Radix plan of the transforms of a pass class (0 the k-space step pass, 1 the
@@ -269,15 +274,14 @@ hmc_status hmc_set_plane_pass(hmc_ctx* ctx, int32_t enable);
  * plan[3] as hmc_set_plan (host arrays, either may be NULL). */
 hmc_status hmc_get_launch(hmc_ctx* ctx, int32_t* grid, int32_t* plan);
 
-/* Autotuner of the launch shapes: for each pass class, times `reps` launches of
- * each candidate (for mixed-size batches one launch per size group, then one
- * launch over the batch with one workgroup per tile or 2, 3, 4, 5, 6, 8, 12
- * workgroups per compute unit) on the context's chains with HIP events and keeps
- * the fastest (in a batch with a size group that has a fused plane pass, the y
- * and real-space classes keep one launch per size group, which the plane pass
- * needs), then, when the chosen launches are single-size and a grid size has
- * alternative plans, times plans 1 to 3 at that grid and keeps the fastest of
- * the four (hmc_set_plan: a plan other than 0 changes rounding); chosen
+/* Autotuner of the launch shapes.  Contexts whose chains can advance in parts
+ * (hmc_set_launch) get the launches the parts need: one launch per size group for
+ * batches of several sizes, one workgroup per tile for the halves of one size.
+ * Otherwise, for each pass class, it times `reps` launches of each candidate (one
+ * workgroup per tile or 2, 3, 4, 5, 6, 8, 12 workgroups per compute unit) on the
+ * context's chains with HIP events and keeps the fastest.  Then, when a grid size
+ * has alternative plans, it times plans 1 to 3 at that launch and keeps the fastest
+ * of the four (hmc_set_plan: a plan other than 0 changes rounding); chosen
  * (host [3], may be NULL) receives the grids in the form hmc_set_launch takes
  * (hmc_get_launch also returns the plans).  The state (delta_hat, p_hat, the
  * parameters) is unchanged; captured graphs are dropped. */

@@ -1289,24 +1289,24 @@ hmc_status hmc_autotune(hmc_ctx* c, int32_t reps, int32_t* chosen) {
     (void)hipEventElapsedTime(ms, a, b);
     return true;
   };
-  // batches whose size groups have a fused plane pass run it only when the y and
-  // real-space classes launch per size group, so those classes keep that launch
-  bool plane_groups = false;
-  for (auto& g : c->groups) plane_groups |= plane_pass_batches(g.n);
-  plane_groups &= c->plane_pass && c->uniform_n == 0;
+  // A context that can advance in parts (see split) keeps the launches its parts need: grids or
+  // whole-batch launches that win a pass timed by itself lose the parts.  Trajectories with the
+  // grids that were picked so, and with these (us): two 192^3 chains 3118 and 2720, six 128^3
+  // 2235 and 2118, two 256^3 6875 and 6538, 2 x 8^3 with 2 x 16^3 416 and 142, 4 x 32^3 with
+  // 4 x 64^3 797 and 621; batches with 128^3 chains and up were picked as here.  Slower: one
+  // 32^3 with one 64^3 chain, 546 where one launch over both takes 493 (the pick took 567).
+  const bool divided = c->parts.size() >= 2;
   for (int cls = 0; cls < 3 && st == HMC_OK; ++cls) {
     float best = 0.f;
     int best_grid = 0;
-    bool best_grouped = false;
     c->plan[cls] = 0;
-    // candidates: one launch per size group (batches of several sizes), then one
-    // launch over the whole batch with each grid
-    const int last = plane_groups && cls > 0 ? 0 : (int)(sizeof(mult) / sizeof(int));
-    for (int cand = c->groups.empty() ? 0 : -1; cand < last; ++cand) {
-      const bool grp = cand < 0;
-      const int grid = grp ? 0 : mult[cand] * cus;
-      if (!grp && mult[cand] > 0 && (grid >= class_tiles(c, cls) || grid % 8 != 0)) continue;
-      c->grouped[cls] = grp;
+    // candidates: one launch per size group (batches of several sizes, always divided), or
+    // one launch over all chains with each grid
+    c->grouped[cls] = !c->groups.empty();
+    const int last = divided ? 1 : (int)(sizeof(mult) / sizeof(int));
+    for (int cand = 0; cand < last; ++cand) {
+      const int grid = mult[cand] * cus;
+      if (mult[cand] > 0 && (grid >= class_tiles(c, cls) || grid % 8 != 0)) continue;
       c->grid[cls] = grid;
       float ms = 0.f;
       if (!time_class(cls, &ms)) {
@@ -1316,14 +1316,12 @@ hmc_status hmc_autotune(hmc_ctx* c, int32_t reps, int32_t* chosen) {
       if (best == 0.f || ms < best) {
         best = ms;
         best_grid = grid;
-        best_grouped = grp;
       }
     }
     c->grid[cls] = best_grid;
-    c->grouped[cls] = best_grouped;
-    if (chosen) chosen[cls] = best_grouped ? -1 : best_grid;
+    if (chosen) chosen[cls] = c->grouped[cls] ? -1 : best_grid;
     // radix plans of the single-size launches at the chosen grid
-    if (st == HMC_OK && any_plans(c) && (c->uniform_n != 0 || best_grouped)) {
+    if (st == HMC_OK && any_plans(c)) {
       int best_plan = 0;
       for (int p = 1; p < kPlanCount; ++p) {
         c->plan[cls] = p;

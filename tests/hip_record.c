@@ -168,8 +168,9 @@ err hipEventSynchronize(void* e) {
   return 0;
 }
 err hipEventElapsedTime(float* ms, void* a, void* b) {
+  static int calls;
   (void)a, (void)b;
-  *ms = 1.f;
+  *ms = 1.f / ++calls; /* each measurement faster than the one before */
   return 0;
 }
 err hipStreamBeginCapture(void* s, int mode) {

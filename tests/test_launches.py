@@ -53,3 +53,22 @@ def test_learned_mass_batch_has_one_form(launch, planes):
     direct, timed, captured = hr.call(learned_forms, launch)
     assert bool(direct) == planes
     assert direct == timed == captured
+
+
+def tuned(sizes, group):
+    c = hr.Context(sizes)
+    if group:
+        c.group()
+    before = hr.streams(c.log()[0])
+    c.autotune()
+    return len(before), [len(hr.streams(c.log(sweep=sweep)[0])) for sweep in (False, True)]
+
+
+@pytest.mark.parametrize("sizes,parts", [([192] * 2, 2), ([128] * 6, 2), ([256] * 3, 2), ([64, 128, 64, 192], 3),
+                                         ([8, 16], 2), ([128] * 5, 1), ([64] * 48, 1), ([256], 1)])
+def test_autotuner_keeps_the_parts(sizes, parts):
+    """Contexts on either side of the sizes from which chains advance in parts, with every
+    launch timed faster than the one before it: the autotuner's last candidate, a grid of its
+    own, would put all chains on one stream."""
+    before, after = hr.call(tuned, sizes, len(set(sizes)) > 1)
+    assert before == parts and after == [parts, parts]
