@@ -80,6 +80,16 @@ hmc_status cnn_train_step(cnn_ctx* ctx, int32_t n, const float* in3, const float
  * context was created, its grid size changed or cnn_forward ran. */
 hmc_status cnn_layer_state(cnn_ctx* ctx, int32_t layer, float* z, float* a, float* dz);
 
+/* The convolutions' bf16 GELU(z) and v GELU'(z), which leave out the last digits of the
+ * normal CDF where the rounding does not need them, against the same with erfcf, for the
+ * float32 z of the `count` bit patterns from `first` on (count a multiple of 4, first + count
+ * <= 2^32) and one v for each of them: 1 (seed 0), or of either sign and a magnitude of 2^-44
+ * to 2^4, chosen by seed.  differ (host [2]): values of GELU and of v GELU' that are not the
+ * same bf16 value; worst (host [2]): the largest deviation before rounding, over the bound
+ * that decides where erfcf is needed (below 1 if the bound holds). */
+hmc_status cnn_gelu_check(cnn_ctx* ctx, uint32_t first, uint64_t count, uint32_t seed,
+                          int64_t* differ, double* worst);
+
 const char* cnn_last_error(const cnn_ctx* ctx);
 void cnn_destroy(cnn_ctx* ctx);
 

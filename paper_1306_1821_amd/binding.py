@@ -52,7 +52,7 @@ EXPORTS = ["hmc_workspace_bytes", "hmc_init", "hmc_init_batch", "leapfrog_trajec
            "hmc_timing", "hmc_use_graph", "hmc_last_error", "hmc_destroy", "shell_power_noalloc",
            "hmc_set_plane_pass",
            "cnn_param_count", "cnn_create", "cnn_get_params", "cnn_forward", "cnn_gradient",
-           "cnn_features", "cnn_layer_state",
+           "cnn_features", "cnn_layer_state", "cnn_gelu_check",
            "cnn_train_step", "cnn_last_error", "cnn_destroy"]
 
 _lib = None
@@ -116,6 +116,7 @@ def lib(path=LIB_PATH):
     L.cnn_features.argtypes = [P, I32, P, ctypes.c_float, P, P, P]
     L.cnn_train_step.argtypes = [P, I32, P, P, ctypes.c_float, D]
     L.cnn_layer_state.argtypes = [P, I32, P, P, P]
+    L.cnn_gelu_check.argtypes = [P, ctypes.c_uint32, U64, ctypes.c_uint32, ctypes.POINTER(ctypes.c_int64), D]
     L.cnn_last_error.argtypes = [P]
     L.cnn_last_error.restype = ctypes.c_char_p
     L.cnn_destroy.argtypes = [P]
@@ -527,6 +528,13 @@ class CNN:
                                            ctypes.c_void_p(dz.data_ptr())))
         f = lambda t: None if t is None else t.cpu().numpy().astype(np.float64)
         return f(z), f(a), f(dz)
+
+    def gelu_check(self, first=0, count=1 << 32, seed=0):
+        """(values of GELU and of v GELU' whose bf16 rounding differs from the erfcf form's,
+        largest deviations over their bounds) for `count` float32 bit patterns; see cnn_gelu_check."""
+        differ, worst = (ctypes.c_int64 * 2)(), (ctypes.c_double * 2)()
+        self._check(self.L.cnn_gelu_check(self.ctx, int(first), int(count), int(seed), differ, worst))
+        return tuple(differ), tuple(worst)
 
     def train_step(self, inputs, target, lr):
         x, t = self._dev(inputs), self._dev(target)
