@@ -31,6 +31,9 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kCin[4] = {3, 16, 16, 16};
 constexpr int kCout[4] = {16, 16, 16, 2};
 constexpr int kTile = 27 * 256;  // entries of one weight-gradient partial
+// weight-gradient partials at most: 3 blocks on each of 256 compute units, and the same number
+// on a device (partition) with fewer, so that a gradient's rounding does not depend on it
+constexpr int kParts = 768;
 
 inline int off_w(int l) {
   int o = 0;
@@ -685,7 +688,6 @@ using namespace cnnk;
 
 struct cnn_ctx {
   hipStream_t stream = nullptr;
-  int parts = 0;  // weight-gradient partials: 3 blocks per compute unit
   std::string err;
   float *p = nullptr, *g = nullptr, *m1 = nullptr, *m2 = nullptr;
   bf16x4* wp[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -787,7 +789,7 @@ hmc_status gradient(cnn_ctx* c, int n, const float* in3, const float* target, do
   const long long nv = (long long)n * n * n;
   hipLaunchKernelGGL(k_loss, dim3(1024), dim3(256), 0, c->stream, nv, (const float2*)c->z[3], target,
                      (uint4*)c->dz[3], c->lpart);
-  const int blocks = std::min(wgrad_bricks(n), c->parts);
+  const int blocks = std::min(wgrad_bricks(n), kParts);
   for (int l = 3; l >= 0; --l) {
     const uint16_t* dz = c->dz[l];
     if (l == 0)
@@ -852,11 +854,6 @@ hmc_status cnn_create(const float* params, void* stream, cnn_ctx** out) {
     return HMC_EDEVICE;
   };
   hipError_t e;
-  int dev = 0;
-  if ((e = hipGetDevice(&dev)) != hipSuccess ||
-      (e = hipDeviceGetAttribute(&c->parts, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess)
-    return bail("device attributes", e);
-  c->parts *= 3;
   // g holds the gradient and, past its end, the last layer's bias padded to 16
   if ((e = hipMalloc(&c->p, np * sizeof(float))) != hipSuccess) return bail("hipMalloc", e);
   if ((e = hipMalloc(&c->g, n_grad() * sizeof(float))) != hipSuccess) return bail("hipMalloc", e);
@@ -867,9 +864,9 @@ hmc_status cnn_create(const float* params, void* stream, cnn_ctx** out) {
       return bail("hipMalloc", e);
     if ((e = hipMalloc(&c->wd[l], 27 * 64 * sizeof(bf16x4))) != hipSuccess) return bail("hipMalloc", e);
   }
-  if ((e = hipMalloc(&c->wpart, (size_t)c->parts * kTile * sizeof(float))) != hipSuccess)
+  if ((e = hipMalloc(&c->wpart, (size_t)kParts * kTile * sizeof(float))) != hipSuccess)
     return bail("hipMalloc", e);
-  if ((e = hipMalloc(&c->dbpart, (size_t)c->parts * 16 * sizeof(float))) != hipSuccess)
+  if ((e = hipMalloc(&c->dbpart, (size_t)kParts * 16 * sizeof(float))) != hipSuccess)
     return bail("hipMalloc", e);
   if ((e = hipMalloc(&c->lpart, 1024 * sizeof(double))) != hipSuccess) return bail("hipMalloc", e);
   if ((e = hipHostMalloc((void**)&c->lpart_h, 1024 * sizeof(double), 0)) != hipSuccess)

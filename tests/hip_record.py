@@ -36,6 +36,11 @@ def call(function, *args):
             return pool.apply_async(function, args).get(timeout=100)
 
 
+def words():
+    """The record since it was cleared, as lists of words."""
+    return [line.split() for line in runtime.record_text().decode().splitlines()]
+
+
 class Context:
     """A sampler of chains of the given grid sizes, on buffers that no kernel touches."""
 
@@ -78,14 +83,14 @@ class Context:
         self.check(lib.hmc_autotune(self.ctx, 2, None))
 
     def log(self, index=1, sweep=False):
-        """What one queued trajectory (or sweep) asks of the runtime, as lists of words, and its status."""
+        """The record of one queued trajectory (or sweep), and its status."""
         runtime.record_clear()
         out = ctypes.c_void_p(1 << 51)
         if sweep:
             st = lib.gibbs_sweep_async(self.ctx, index, out)
         else:
             st = lib.leapfrog_trajectory_async(self.ctx, index, out, out)
-        return [line.split() for line in runtime.record_text().decode().splitlines()], st
+        return words(), st
 
     def close(self):
         lib.hmc_destroy(self.ctx)

@@ -1,5 +1,6 @@
 """Which kernels a context launches, on which streams, and how these are joined: against a HIP
 runtime that only writes down what it is asked (no GPU)."""
+import ctypes
 import re
 
 import pytest
@@ -72,3 +73,22 @@ def test_autotuner_keeps_the_parts(sizes, parts):
     own, would put all chains on one stream."""
     before, after = hr.call(tuned, sizes, len(set(sizes)) > 1)
     assert before == parts and after == [parts, parts]
+
+
+def weight_gradient_blocks(units):
+    hr.runtime.record_compute_units(units)
+    params = (ctypes.c_float * hr.lib.cnn_param_count())()
+    net, field = ctypes.c_void_p(), ctypes.c_void_p(1 << 50)
+    assert hr.lib.cnn_create(params, ctypes.c_void_p(hr.STREAM), ctypes.byref(net)) == binding.HMC_OK
+    out = []
+    for n in (16, 128):
+        hr.runtime.record_clear()
+        assert hr.lib.cnn_gradient(net, n, field, field, None, None) == binding.HMC_OK
+        out.append([w[2] for w in hr.words() if w[0] == "launch" and "k_wgrad" in w[3]])
+    return out
+
+
+def test_weight_gradient_sums_are_split_alike_on_every_device():
+    """The partial sums of a weight gradient, and so its rounding, follow from the grid size alone."""
+    whole = hr.call(weight_gradient_blocks, 256)
+    assert whole == hr.call(weight_gradient_blocks, 32) and len(whole[0]) == len(whole[1]) == 4
