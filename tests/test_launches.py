@@ -92,3 +92,24 @@ def test_weight_gradient_sums_are_split_alike_on_every_device():
     """The partial sums of a weight gradient, and so its rounding, follow from the grid size alone."""
     whole = hr.call(weight_gradient_blocks, 256)
     assert whole == hr.call(weight_gradient_blocks, 32) and len(whole[0]) == len(whole[1]) == 4
+
+
+def small_forms(sizes, group):
+    c = hr.Context(sizes, rj=True)
+    if group:
+        c.group()
+    out = []
+    for timing, graph in ((False, False), (False, True), (True, False)):
+        c.timing(timing)
+        c.graph(graph)
+        log, _ = c.log(sweep=True)
+        out.append([sum(name in k for k in hr.kernels(log)) for name in ("k_small_trajectory", "k_small_joint")])
+    return out
+
+
+@pytest.mark.parametrize("sizes,group,launches", [([8] * 2, False, 1), ([16], False, 1), ([8, 16, 32], True, 2),
+                                                  ([8, 16, 32], False, 0), ([32] * 2, False, 0)])
+def test_small_grids_run_in_one_workgroup(sizes, group, launches):
+    """The one-workgroup trajectory and joint move, direct and captured; the passes while timed."""
+    direct, captured, timed = hr.call(small_forms, sizes, group)
+    assert direct == captured == [launches, launches] and timed == [0, 0]
