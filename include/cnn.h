@@ -50,7 +50,9 @@ hmc_status cnn_create(const float* params, void* stream, cnn_ctx** out);
 hmc_status cnn_get_params(cnn_ctx* ctx, float* params);
 
 /* Forward pass.  in3: device [3][N^3] (channel 0 normalised data, 1 mask,
- * 2 selection); mu, logvar: device [N^3] outputs (either may be NULL). */
+ * 2 selection); mu, logvar: device [N^3] outputs (either may be NULL).  The last
+ * layer sums its products in another order than in training, so mu and logvar are those
+ * of a gradient evaluation (cnn_layer_state, layer 3) to float32 rounding, not bit for bit. */
 hmc_status cnn_forward(cnn_ctx* ctx, int32_t n, const float* in3, float* mu, float* logvar);
 
 /* Network inputs from the survey: out3 (device [3][N^3]) receives

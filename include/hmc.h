@@ -28,7 +28,8 @@
  *    lambda_m = P_m N^3 / L^3.
  *  - Ownership: the caller owns every device buffer (inputs, state, the
  *    workspace); the library owns only host-side objects inside hmc_ctx and a
- *    few small device tables it allocates at init (freed by hmc_destroy).
+ *    few small device tables it allocates at init (freed by hmc_destroy), and keeps
+ *    at most eight idle streams of closed contexts for the next ones.
  *    Device pointers are plain HIP device addresses; `stream` is a hipStream_t
  *    (void* here so that the header needs no HIP include).  All device work is
  *    stream-ordered on that stream.  Calls that return host scalars
@@ -354,7 +355,11 @@ hmc_status hmc_use_graph(hmc_ctx* ctx, int32_t enable);
 
 /* Device timing of the leapfrog passes (tracing).  enable = 1 starts
  * recording HIP events on the context's stream around every launch of the
- * step passes and clears the totals; enable = 0x10 | mask | (s << 8) does the
+ * step passes and clears the totals (while it records, trajectories and sweeps launch every
+ * pass by itself on that stream: contexts and size groups of 8^3 and 16^3 chains, which else
+ * run a trajectory or joint move in one launch, and chains that else advance in parts,
+ * hmc_set_launch, are timed in that form; results are the same bit for bit, the wall time
+ * of a call is not); enable = 0x10 | mask | (s << 8) does the
  * same for the classes whose bits (1 << class) are set in mask, around every
  * (s + 1)-th launch of each class only (s < 256; fewer events, less
  * perturbation); enable = 0 stops recording; enable = -1 only reads.  Other

@@ -1477,7 +1477,9 @@ __device__ __forceinline__ void yzpass(const ChainDev& d, int x, const ZArgs a, 
 // single-size launch: N / PP consecutive workgroups per chain, PP x planes each
 // At 128^3 the register cap puts two workgroups on a compute unit, one's memory phases over
 // the other's transforms (four chains: learned force 40.5 -> 35.5 us, data force with the energy
-// 45.1 -> 38.6; the learned force's energy instantiation spills under it and goes without)
+// 45.1 -> 38.6; the learned force's energy instantiation spills under it and goes without).  The
+// plain step's pass is as fast either way (one chain 20.2 and 20.2 us, four 31.7 and 31.6;
+// trajectories of eight chains 4087 -> 4053)
 template <int N, bool FULL, int KIND>
 constexpr int yz_waves() { return N == 128 && !(FULL && KIND == YZ_FORCE) ? 4 : 1; }
 template <int N, bool FULL, int KIND = YZ_DATA>

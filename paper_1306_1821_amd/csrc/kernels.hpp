@@ -74,8 +74,8 @@ bool plane_pass_supported(int n);  // contexts of one grid size
 bool plane_pass_batches(int n);    // size groups of a batch
 void launch_yzpass(const ChainDev* ch, int nch, ZArgs a, const float2* tw, hipStream_t s, int n,
                    int kind = YZ_DATA);
-// grids whose trajectories and joint moves run in one workgroup per chain (single-size
-// contexts); launch_small_joint follows launch_rj(RJ_BEGIN)
+// grids whose trajectories and joint moves run in one workgroup per chain (contexts of one size,
+// and the size groups of divided batches); launch_small_joint follows launch_rj(RJ_BEGIN)
 bool small_grid_supported(int n);
 void launch_small_trajectory(const ChainDev* ch, int nch, int steps, const float2* tw, hipStream_t s,
                              int n);

@@ -69,7 +69,7 @@ struct Chain {
   std::vector<double> hp;  // host mirror of the parameter block
 };
 
-// a context of one grid size runs in two parts from this many voxels on (see split)
+// a context of one grid size, 128^3 up, runs in two parts from this many voxels on (see split)
 constexpr long long kSplitVoxels = 12000000;
 
 struct WsLayout {
@@ -855,12 +855,14 @@ static void trajectory(Seq& q) {
 // branches of a captured graph): the launches of one part fill the gaps, ramps and
 // last rounds of the others'.  A batch splits into its size groups where every pass class runs
 // one launch per group (8 x 64^3, 6 x 128^3 and 2 x 192^3, sweep with the joint move: 19.5 ->
-// 16.3 ms).  A context of one size splits into halves from kSplitVoxels on: two 192^3 chains
-// 4.55 -> 3.84 ms a trajectory (their 384 planes are one and a half rounds of the compute
-// units), two 256^3 chains 6.82 -> 6.64, six 128^3 chains 2.35 -> 2.16; below it the
-// launches' own time is what a step takes (two 128^3 chains 0.92 -> 1.10, eight 64^3 chains
-// 0.85 -> 0.95, four 128^3 chains' sweeps 4.71 -> 4.88).  A chain's results do not depend on
-// its part.
+// 16.3 ms).  A context of one size splits into halves from kSplitVoxels on.  Trajectories of 20
+// steps, whole -> halves (us): 128^3 x 2 918 -> 1068, x 4 1487 -> 1523, x 5 1905 -> 1890 (the
+// sweep 4131 -> 4152), x 6 2369 -> 2115, x 8 3134 -> 2857; 192^3 x 2 3168 -> 2719 (their 384
+// planes are one and a half rounds of the compute units), x 3 4827 -> 4628; 256^3 x 2 6749 ->
+// 6458, x 3 10296 -> 9979.  With little work a step takes the launches' own time, twice on two
+// streams; the line lies between five 128^3 chains (10.5 M voxels) and six (12.6 M).  64^3 and
+// smaller stay whole: 64^3 x 16 884 -> 953, x 48 (12.6 M) 2249 -> 2233 but the sweep 4659 ->
+// 4699, x 64 3217 -> 3087.  A chain's results do not depend on its part.
 static bool split(const hmc_ctx* c) {
   if (c->parts.size() < 2 || c->timing) return false;
   if (c->uniform_n != 0) return !c->grid[0] && !c->grid[1] && !c->grid[2];
