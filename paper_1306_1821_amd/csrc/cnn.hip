@@ -174,14 +174,13 @@ __global__ void __launch_bounds__(256) k_features(long long nv, const float* __r
 
 enum ConvMode : int { C_FWD_GELU = 0, C_FWD_LAST = 1, C_DGRAD = 2 };
 
-// Bricks of the convolutions: BX x BY x 16 voxels (x, y, z) with a one-voxel halo, staged
+// Bricks of the convolutions: 4 x CY x 16 voxels (x, y, z) with a one-voxel halo, staged
 // in LDS; every grid side is a multiple of 4, so only y and z can overhang.
-constexpr int kCX = 4, kCY = 8, kBZ = 16;
-constexpr int kCHX = kCX + 2, kCHY = kCY + 2, kHZ = kBZ + 2;
-constexpr int kCHalo = kCHX * kCHY * kHZ;  // voxels of the haloed brick
+constexpr int kCX = 4, kBZ = 16;
+constexpr int kCHX = kCX + 2, kHZ = kBZ + 2;
 
-__host__ __device__ inline int conv_bricks(int n) {
-  return (n / kCX) * ((n + kCY - 1) / kCY) * ((n + kBZ - 1) / kBZ);
+__host__ __device__ inline int conv_bricks(int n, int cy) {
+  return (n / kCX) * ((n + cy - 1) / cy) * ((n + kBZ - 1) / kBZ);
 }
 
 // Workgroups are dealt to the 8 XCDs round-robin; brick_of gives each XCD a contiguous
@@ -191,8 +190,9 @@ __device__ __forceinline__ int brick_of(int b, int g) {
   return x < r ? x * (q + 1) + i : r * (q + 1) + (x - r) * q + i;
 }
 
-// One 3x3x3 convolution (zero padding).  Wave w of a block owns the brick's x plane w: 8
-// rows of 16 z voxels, one accumulator tile each.  The weights are the MFMA's A operand
+// One 3x3x3 convolution (zero padding).  Wave w of a block owns the brick's x plane w: CY
+// rows (8, or 2 on small grids, see conv_rows) of 16 z voxels, one accumulator tile each; the
+// counts below are for 8.  The weights are the MFMA's A operand
 // (rows = output channels) and a row's shifted activations its B operand (columns =
 // voxels), so a lane ends up with 4 consecutive output channels of one voxel and stores
 // them together (64 lanes cover 16 whole voxels; with the operands the other way round a
@@ -218,20 +218,21 @@ __device__ __forceinline__ int brick_of(int b, int g) {
 // before that).  A forward at 256^3 went from 1648 to 1540 us with the last layer's form.
 // TRAIN: keep the pre-activation for the backward pass.  LAST: out0, out1 are the two
 // output channels, or out0 the pairs [V][2] for the loss (TRAIN).
-template <int CS, int MODE, bool TRAIN>
+template <int CS, int MODE, bool TRAIN, int CY>
 __global__ void __launch_bounds__(256, 4) k_conv(int n, const void* __restrict__ in,
                                                  const bf16x4* __restrict__ wp,
                                                  const float* __restrict__ bias,
                                                  const float* __restrict__ zprev,
                                                  float* __restrict__ out0, float* __restrict__ out1,
                                                  uint16_t* __restrict__ aout) {
+  constexpr int kCHY = CY + 2, kCHalo = kCHX * kCHY * kHZ;  // voxels of the haloed brick
   constexpr int kItems = CS == 16 ? 2 * kCHalo : kCHalo;  // 16-byte halves / whole voxels
   constexpr int kIter = (kItems + 255) / 256;
   __shared__ uint4 brick[CS == 16 ? 2 * kCHalo : kCHalo / 2];  // [channel half][voxel] / [voxel][4]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int nbz = (n + kBZ - 1) / kBZ, nby = (n + kCY - 1) / kCY;
+  const int nbz = (n + kBZ - 1) / kBZ, nby = (n + CY - 1) / CY;
   const int bk = brick_of(blockIdx.x, gridDim.x);
-  const int x0 = bk / (nbz * nby) * kCX, y0 = bk / nbz % nby * kCY, z0 = bk % nbz * kBZ;
+  const int x0 = bk / (nbz * nby) * kCX, y0 = bk / nbz % nby * CY, z0 = bk % nbz * kBZ;
   const long long nv = (long long)n * n * n;
   // stage the brick with its halo (zeros outside the grid), every load first
   uint4 st[CS == 16 ? kIter : 1];
@@ -282,7 +283,7 @@ __global__ void __launch_bounds__(256, 4) k_conv(int n, const void* __restrict__
   const int m = lane & 15, grp = lane >> 4;
   const bf16x4* lb = reinterpret_cast<const bf16x4*>(brick);
   const int ofs = (grp >> 1) * 2 * kCHalo + (grp & 1);  // the lane's 4 channels (CS = 16)
-  constexpr int kRows = kPairs ? kCHY : kCY;
+  constexpr int kRows = kPairs ? kCHY : CY;
   f32x4 acc[kRows];
 #pragma unroll
   for (int r = 0; r < kRows; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -304,7 +305,7 @@ __global__ void __launch_bounds__(256, 4) k_conv(int n, const void* __restrict__
           w[0], lb[(((wave + 2) * kCHY + hy) * kHZ + m + 2) * 2 + ofs], acc[hy], 0, 0, 0);
     // rows (dy, channel): dy 0 and 1 in the lanes of group 0, dy 2 in those of group 1
 #pragma unroll
-    for (int r = 0; r < kCY; ++r)
+    for (int r = 0; r < CY; ++r)
 #pragma unroll
       for (int o = 0; o < 2; ++o)
         acc[r][o] = (acc[r][o] + acc[r + 1][2 + o]) + __shfl_xor(acc[r + 2][o], 16);
@@ -317,7 +318,7 @@ __global__ void __launch_bounds__(256, 4) k_conv(int n, const void* __restrict__
         for (int dz = 0; dz < 3; ++dz) {
           const bf16x4 b = lb[(((wave + dx) * kCHY + hy) * kHZ + m + dz) * 2 + ofs];
 #pragma unroll
-          for (int r = 0; r < kCY; ++r)
+          for (int r = 0; r < CY; ++r)
             if (r <= hy && hy <= r + 2)
               acc[r] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w[(dx * 3 + hy - r) * 3 + dz], b, acc[r], 0, 0, 0);
         }
@@ -327,7 +328,7 @@ __global__ void __launch_bounds__(256, 4) k_conv(int n, const void* __restrict__
       const int tap = 4 * c + grp;
       const int at = tap < 27 ? (tap / 9 * kCHY + tap / 3 % 3) * kHZ + tap % 3 : 0;
 #pragma unroll
-      for (int r = 0; r < kCY; ++r) {
+      for (int r = 0; r < CY; ++r) {
         bf16x4 b = lb[(wave * kCHY + r) * kHZ + m + at];
         if (c == NC - 1 && tap >= 27) b = bf16x4{0, 0, 0, 0};
         acc[r] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w[c], b, acc[r], 0, 0, 0);
@@ -338,7 +339,7 @@ __global__ void __launch_bounds__(256, 4) k_conv(int n, const void* __restrict__
   if (MODE != C_DGRAD) bi = *reinterpret_cast<const float4*>(bias + 4 * grp);
   const int zz = z0 + m;
 #pragma unroll
-  for (int r = 0; r < kCY; ++r) {
+  for (int r = 0; r < CY; ++r) {
     if (y0 + r >= n || zz >= n) continue;
     const long long v = ((long long)(x0 + wave) * n + y0 + r) * n + zz;
     const float val[4] = {acc[r][0] + bi.x, acc[r][1] + bi.y, acc[r][2] + bi.z, acc[r][3] + bi.w};
@@ -723,6 +724,14 @@ hmc_status cfail(cnn_ctx* c, hmc_status st, const std::string& why) {
 
 int nchunk_fwd(int l) { return l == 0 ? 7 : 27; }
 
+// y rows of a brick: 2 where bricks of 8 rows would be fewer than the 256 compute units (up to
+// 48^3), so that a small grid spreads over more of them and a wave's chain of products, GELU and
+// stores is a quarter as long.  Forward (us), 8 and 2 rows: 8^3 31.9 and 18.0, 20^3 35.8 and
+// 18.6, 32^3 34.1 and 19.3, 48^3 35.8 and 29.1, 64^3 45.0 and 45.1, 128^3 198 and 242 (a brick
+// of 2 rows reads its halo for a quarter of the voxels); training steps 20^3 247 and 184, 48^3
+// 268 and 244, 128^3 905 and 1064.
+int conv_rows(int n) { return conv_bricks(n, 8) < 256 ? 2 : 8; }
+
 hmc_status pack_all(cnn_ctx* c) {
   for (int l = 0; l < 4; ++l) {
     const int nc = nchunk_fwd(l);
@@ -758,18 +767,26 @@ hmc_status ensure(cnn_ctx* c, int n) {
   return HMC_OK;
 }
 
+template <int CS, int MODE, bool TRAIN, class... Args>
+void launch_conv(cnn_ctx* c, int n, Args... args) {
+  const int cy = conv_rows(n);
+  const dim3 g(conv_bricks(n, cy)), b(256);
+  if (cy == 8)
+    hipLaunchKernelGGL((k_conv<CS, MODE, TRAIN, 8>), g, b, 0, c->stream, n, args...);
+  else
+    hipLaunchKernelGGL((k_conv<CS, MODE, TRAIN, 2>), g, b, 0, c->stream, n, args...);
+}
+
 // TRAIN: keeps the pre-activations; out0 / out1: see k_conv
 template <bool TRAIN>
 hmc_status forward_t(cnn_ctx* c, int n, const float* in3, float* mu, float* logvar) {
-  const dim3 g(conv_bricks(n)), b(256);
-  hipLaunchKernelGGL((k_conv<4, C_FWD_GELU, TRAIN>), g, b, 0, c->stream, n, in3, c->wp[0],
-                     c->p + off_b(0), nullptr, c->z[0], nullptr, c->a[0]);
+  launch_conv<4, C_FWD_GELU, TRAIN>(c, n, in3, c->wp[0], c->p + off_b(0), nullptr, c->z[0], nullptr, c->a[0]);
   for (int l = 1; l < 3; ++l)
-    hipLaunchKernelGGL((k_conv<16, C_FWD_GELU, TRAIN>), g, b, 0, c->stream, n, c->a[l - 1],
-                       c->wp[l], c->p + off_b(l), nullptr, c->z[l], nullptr, c->a[l]);
+    launch_conv<16, C_FWD_GELU, TRAIN>(c, n, c->a[l - 1], c->wp[l], c->p + off_b(l), nullptr, c->z[l], nullptr,
+                                       c->a[l]);
   // last layer: bias padded to 16 channels (a device copy past the gradient)
-  hipLaunchKernelGGL((k_conv<16, C_FWD_LAST, TRAIN>), g, b, 0, c->stream, n, c->a[2], c->wp[3],
-                     c->g + off_pad(), nullptr, TRAIN ? c->z[3] : mu, logvar, nullptr);
+  launch_conv<16, C_FWD_LAST, TRAIN>(c, n, c->a[2], c->wp[3], c->g + off_pad(), nullptr, TRAIN ? c->z[3] : mu,
+                                     logvar, nullptr);
   CCHK(c, hipGetLastError());
   return HMC_OK;
 }
@@ -801,8 +818,7 @@ hmc_status gradient(cnn_ctx* c, int n, const float* in3, const float* target, do
     hipLaunchKernelGGL(k_wreduce, dim3(kRedBlocks + 1), dim3(1024), 0, c->stream, c->wpart,
                        c->dbpart, blocks, kCin[l], kCout[l], c->g + off_w(l), c->g + off_b(l));
     if (l > 0)
-      hipLaunchKernelGGL((k_conv<16, C_DGRAD, true>), dim3(conv_bricks(n)), dim3(256), 0, c->stream,
-                         n, dz, c->wd[l], nullptr, c->z[l - 1], nullptr, nullptr, c->dz[l - 1]);
+      launch_conv<16, C_DGRAD, true>(c, n, dz, c->wd[l], nullptr, c->z[l - 1], nullptr, nullptr, c->dz[l - 1]);
   }
   CCHK(c, hipGetLastError());
   CCHK(c, hipMemcpyAsync(c->lpart_h, c->lpart, 1024 * sizeof(double), hipMemcpyDeviceToHost,

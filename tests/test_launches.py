@@ -113,3 +113,24 @@ def test_small_grids_run_in_one_workgroup(sizes, group, launches):
     """The one-workgroup trajectory and joint move, direct and captured; the passes while timed."""
     direct, captured, timed = hr.call(small_forms, sizes, group)
     assert direct == captured == [launches, launches] and timed == [0, 0]
+
+
+def convolution_blocks(sizes):
+    params = (ctypes.c_float * hr.lib.cnn_param_count())()
+    net, field = ctypes.c_void_p(), ctypes.c_void_p(1 << 50)
+    assert hr.lib.cnn_create(params, ctypes.c_void_p(hr.STREAM), ctypes.byref(net)) == binding.HMC_OK
+    out = []
+    for n in sizes:
+        hr.runtime.record_clear()
+        assert hr.lib.cnn_forward(net, n, field, field, field) == binding.HMC_OK
+        assert hr.lib.cnn_gradient(net, n, field, field, None, None) == binding.HMC_OK
+        out.append([int(w[2]) for w in hr.words() if w[0] == "launch" and "k_conv" in w[3]])
+    return out
+
+
+def test_small_convolutions_spread_over_the_compute_units():
+    """Four layers forward, four in training and three backward: at least a workgroup for every
+    four x planes, two y rows and sixteen z voxels, or for every compute unit."""
+    sizes = range(4, 133, 4)
+    for n, blocks in zip(sizes, hr.call(convolution_blocks, list(sizes))):
+        assert len(blocks) == 11 and min(blocks) >= min(256, n // 4 * (n // 2) * -(-n // 16)), (n, blocks)
