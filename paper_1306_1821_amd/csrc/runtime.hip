@@ -133,6 +133,7 @@ bool valid_cfg(const hmc_config* c, std::string* why) {
 struct hmc_ctx {
   std::vector<Chain> ch;
   hipStream_t stream = nullptr;
+  ChainDev* desc = nullptr;   // every descriptor array below (see desc_arrays)
   ChainDev* d_all = nullptr;
   float2* tw = nullptr;
   double* P_all = nullptr;   // every chain's parameter block, back to back
@@ -375,34 +376,34 @@ static hmc_status refresh_gradient(hmc_ctx* c, bool write_dr) {
   return check_launch(c);
 }
 
+// The descriptor arrays of a context lie back to back in one device block (desc), so that a
+// change of any chain's is one copy: all chains, each chain alone, the size groups, the parts.
+// Here the pointer to each array and its chains, in that order.
+static std::vector<std::pair<ChainDev**, std::vector<int>>> desc_arrays(hmc_ctx* c) {
+  std::vector<std::pair<ChainDev**, std::vector<int>>> out(1, {&c->d_all, {}});
+  for (size_t i = 0; i < c->ch.size(); ++i) {
+    out[0].second.push_back((int)i);
+    out.push_back({&c->ch[i].solo, {(int)i}});
+  }
+  for (auto& g : c->groups) out.push_back({&g.d, g.members});
+  for (auto& g : c->parts) out.push_back({&g.d, g.members});
+  return out;
+}
+
 static hmc_status upload_desc(hmc_ctx* c) {
-  std::vector<ChainDev> all(c->ch.size());
-  for (size_t i = 0; i < c->ch.size(); ++i) all[i] = c->ch[i].dev;
-  HIPCHK(c, hipMemcpyAsync(c->d_all, all.data(), all.size() * sizeof(ChainDev),
-                           hipMemcpyHostToDevice, c->stream));
-  for (auto& k : c->ch) {
-    ChainDev s = k.dev;
-    for (int j = 0; j < kTileClasses; ++j) s.tb[j] = 0;
-    HIPCHK(c, hipMemcpyAsync(k.solo, &s, sizeof(ChainDev), hipMemcpyHostToDevice, c->stream));
-  }
-  std::vector<hmc_ctx::Group*> lists;
-  for (auto& g : c->groups) lists.push_back(&g);
-  for (auto& g : c->parts) lists.push_back(&g);
-  for (auto* gp : lists) {
-    auto& g = *gp;
-    std::vector<ChainDev> gd;
-    int base[kTileClasses] = {0, 0, 0, 0};
-    for (int i : g.members) {
-      ChainDev s = c->ch[i].dev;
+  std::vector<ChainDev> all;
+  for (auto& a : desc_arrays(c)) {
+    int base[kTileClasses] = {0, 0, 0, 0};  // first tiles, from zero in every array
+    for (int i : a.second) {
+      all.push_back(c->ch[i].dev);
       for (int j = 0; j < kTileClasses; ++j) {
-        s.tb[j] = base[j];
-        base[j] += s.nt[j];
+        all.back().tb[j] = base[j];
+        base[j] += all.back().nt[j];
       }
-      gd.push_back(s);
     }
-    HIPCHK(c, hipMemcpyAsync(g.d, gd.data(), gd.size() * sizeof(ChainDev), hipMemcpyHostToDevice,
-                             c->stream));
   }
+  HIPCHK(c, hipMemcpyAsync(c->desc, all.data(), all.size() * sizeof(ChainDev), hipMemcpyHostToDevice,
+                           c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   return HMC_OK;
 }
@@ -517,11 +518,8 @@ void hmc_destroy(hmc_ctx* ctx) {
   for (auto& k : ctx->ch) {
     (void)hipFree(k.dev.tf);
     (void)hipFree(k.dev.td);
-    (void)hipFree(k.solo);
   }
-  (void)hipFree(ctx->d_all);
-  for (auto& g : ctx->groups) (void)hipFree(g.d);
-  for (auto& g : ctx->parts) (void)hipFree(g.d);
+  (void)hipFree(ctx->desc);
   for (auto st : ctx->side) give_stream(ctx->dev, st);
   for (auto e : ctx->side_ev) (void)hipEventDestroy(e);
   (void)hipFree(ctx->tw);
@@ -646,8 +644,7 @@ hmc_status hmc_init_batch(const hmc_config* cfg, const hmc_buffers* buf, int32_t
     d.obs = (unsigned long long*)(w + L.obs);
     d.P = c->P_all + (size_t)i * kPSize;
     if (hipMalloc(&d.tf, kTSize * sizeof(float)) != hipSuccess ||
-        hipMalloc(&d.td, kDSize * sizeof(double)) != hipSuccess ||
-        hipMalloc(&k.solo, sizeof(ChainDev)) != hipSuccess) {
+        hipMalloc(&d.td, kDSize * sizeof(double)) != hipSuccess) {
       c->err = "hipMalloc shell tables";
       return bail(HMC_EDEVICE);
     }
@@ -679,10 +676,6 @@ hmc_status hmc_init_batch(const hmc_config* cfg, const hmc_buffers* buf, int32_t
   c->uniform_n = c->ch[0].cfg.n;
   for (auto& k : c->ch)
     if (k.cfg.n != c->uniform_n) c->uniform_n = 0;
-  if (hipMalloc(&c->d_all, n_chains * sizeof(ChainDev)) != hipSuccess) {
-    c->err = "hipMalloc descriptors";
-    return bail(HMC_EDEVICE);
-  }
   if (c->uniform_n == 0) {
     for (int i = 0; i < n_chains; ++i) {
       const int n = c->ch[i].cfg.n;
@@ -697,15 +690,9 @@ hmc_status hmc_init_batch(const hmc_config* cfg, const hmc_buffers* buf, int32_t
       it->nch += 1;
       for (int j = 0; j < kTileClasses; ++j) it->total[j] += c->ch[i].dev.nt[j];
     }
-    for (auto& g : c->groups)
-      if (hipMalloc(&g.d, g.nch * sizeof(ChainDev)) != hipSuccess) {
-        c->err = "hipMalloc group descriptors";
-        return bail(HMC_EDEVICE);
-      }
   }
   if (c->uniform_n == 0) {
     c->parts = c->groups;
-    for (auto& g : c->parts) g.d = nullptr;
   } else if (n_chains >= 2 && c->uniform_n >= 128 && n_chains * c->ch[0].dev.nv >= kSplitVoxels) {
     c->parts.resize(2);
     for (int i = 0; i < n_chains; ++i) {
@@ -716,18 +703,31 @@ hmc_status hmc_init_batch(const hmc_config* cfg, const hmc_buffers* buf, int32_t
       for (int j = 0; j < kTileClasses; ++j) g.total[j] += c->ch[i].dev.nt[j];
     }
   }
+  {
+    const auto arrays = desc_arrays(c);
+    size_t count = 0;
+    for (auto& a : arrays) count += a.second.size();
+    if (hipMalloc(&c->desc, count * sizeof(ChainDev)) != hipSuccess) {
+      c->err = "hipMalloc descriptors";
+      return bail(HMC_EDEVICE);
+    }
+    ChainDev* at = c->desc;
+    for (auto& a : arrays) {
+      *a.first = at;
+      at += a.second.size();
+    }
+  }
   for (size_t i = 0; i < c->parts.size(); ++i) {
     hipEvent_t e = nullptr;
     hipStream_t st = nullptr;
-    bool ok = hipMalloc(&c->parts[i].d, c->parts[i].nch * sizeof(ChainDev)) == hipSuccess &&
-              hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
+    bool ok = hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
     if (e) c->side_ev.push_back(e);
     if (ok && i > 0) {
       ok = take_stream(&st) == hipSuccess && hipGetDevice(&c->dev) == hipSuccess;
       if (st) c->side.push_back(st);
     }
     if (!ok) {
-      c->err = "part descriptors, events or streams";
+      c->err = "events or streams of the parts";
       return bail(HMC_EDEVICE);
     }
   }

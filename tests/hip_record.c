@@ -100,6 +100,7 @@ err hipHostMalloc(void** p, size_t n, unsigned flags) {
 }
 err hipHostFree(void* p) { return hipFree(p); }
 static err copy(void* dst, const void* src, size_t n, int kind) {
+  LOG("copy %d %zu", kind, n);
   if (kind == 1) memcpy(dst, src, n); /* host to device */
   if (kind == 2)
     for (size_t i = 0; i < n / 8; ++i) ((double*)dst)[i] = 1.0;

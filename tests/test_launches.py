@@ -94,6 +94,24 @@ def test_weight_gradient_sums_are_split_alike_on_every_device():
     assert whole == hr.call(weight_gradient_blocks, 32) and len(whole[0]) == len(whole[1]) == 4
 
 
+def copies(sizes):
+    c = hr.Context(sizes)
+    out = []
+    for change in (lambda: hr.lib.hmc_set_step(c.ctx, 0, ctypes.c_double(0.1)),
+                   lambda: hr.lib.hmc_set_mass(c.ctx, len(sizes) - 1, ctypes.c_void_p(1 << 50))):
+        hr.runtime.record_clear()
+        c.check(change())
+        out.append(sum(w[0] == "copy" for w in hr.words()))
+    return out
+
+
+@pytest.mark.parametrize("sizes", [[64], GROUPS, [192] * 2, [8] * 3])
+def test_a_changed_chain_is_one_copy(sizes):
+    """Step size and mass live in the chains' descriptors: however many arrays of them a
+    context has (all chains, size groups, parts), a change goes to the device at once."""
+    assert hr.call(copies, sizes) == [1, 1]
+
+
 def small_forms(sizes, group):
     c = hr.Context(sizes, rj=True)
     if group:
