@@ -234,8 +234,8 @@ hmc_status hmc_warm_start(hmc_ctx* ctx, int32_t chain, const float* mu_dev,
  * multiple of 8 keeps each XCD on a contiguous run of tiles), 0 for one
  * workgroup per tile (the default), or -1 for one single-size launch per grid
  * size of a mixed-size batch (one workgroup per tile each; the same as 0 when
- * every chain has one size).  Results do not depend on it bit for bit, but for one
- * thing: with -1 for the y and the real-space class the size groups of a batch run
+ * every chain has one size).  Results are the same bit for bit for every setting, but
+ * for one thing: with -1 for the y and the real-space class the size groups of a batch run
  * the plane pass where they have one (hmc_set_plane_pass: float32 rounding).
  * Chains advance in parts, each on a stream of its own between the call's start and
  * end in the caller's stream: the size groups of a batch while all three classes are
